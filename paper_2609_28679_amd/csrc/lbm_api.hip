@@ -30,6 +30,7 @@ struct lbm_ctx {
   int codec = -1;    // reduced storage: 0 = bfloat16, 1 = float16 (scaled); -1 = none
   float s_enc = 1.0f, s_dec = 1.0f;
   int planes = 9;    // stored population planes per buffer
+  bool multi = false;  // several steps per launch, from one buffer into the other
   bool aa = false;   // one buffer, in place (isothermal model): layout alternates with t parity
   DdfParams dp{};
   double* fld = nullptr;  // D3Q27 double distribution: derivative fields
@@ -41,7 +42,7 @@ struct lbm_ctx {
   size_t ws_bytes = 0;
   bool own_ws = false;
   void* A = nullptr;  // post-collision populations of the current time
-  void* B = nullptr;  // second buffer of the two-buffer layout (NULL with one buffer)
+  void* B = nullptr;  // second buffer (in-place layout: the read-out area or NULL)
   double* partials = nullptr;  // per-workgroup diagnostics partial sums
   int partial_slots = 0;
   double* history = nullptr;   // ring of kHistoryCap rows {t, totals[5]}
@@ -105,7 +106,7 @@ struct Plan {
   int D, Q, kind, planes, codec;
   size_t off_fld;  // D3Q27 double distribution: derivative fields (8 planes of the storage type)
   size_t off_nb;   // non-equilibrium extrapolation walls: boundary rows (2D) or planes (3D)
-  bool ddf, aa;
+  bool ddf, aa, multi;
   Layout L;
   Grid G;
   size_t elem;
@@ -261,6 +262,9 @@ void make_plan(const lbm_params* p, Plan& P) {
   const size_t one_buffer = (size_t)P.planes * P.L.plane * P.elem;
   P.aa = aa_ok && (p->streaming == LBM_STREAM_ONE_BUFFER ||
                    (p->streaming == LBM_STREAM_AUTO && one_buffer <= ((size_t)384 << 20)));
+  // several steps per launch read one buffer and write another (isothermal D2Q9; rows up to
+  // 2^24 nodes, which the launch's 32-bit row offsets and thread count are good for)
+  P.multi = aa_ok && P.D == 2 && p->streaming != LBM_STREAM_ONE_BUFFER && p->nx <= 1 << 24;
   size_t off = 0;
   // reduced storage: float32 moment planes + uint16 non-equilibrium planes
   // (isothermal: 3 + 6, double distribution: 4 + 6 + 8)
@@ -271,7 +275,11 @@ void make_plan(const lbm_params* p, Plan& P) {
   P.off_B = off; if (!P.aa) off = align_up(off + pop, 256);
   P.off_part = off; off = align_up(off + (size_t)P.partial_slots * kDiagValues * 8, 256);
   P.off_hist = off; off = align_up(off + (size_t)kHistoryCap * 6 * 8, 256);
-  P.off_read = off; off = align_up(off + (size_t)P.L.nodes() * (P.D + 3) * 8, 256);
+  // The in-place layout has no second buffer: several steps per launch go to the read-out area,
+  // which holds nothing between calls (40 bytes per node against 36 of the float32 state), and
+  // back (see multi_launches).
+  const size_t readout = (size_t)P.L.nodes() * (P.D + 3) * 8;
+  P.off_read = off; off = align_up(off + (P.aa && P.multi ? std::max(readout, pop) : readout), 256);
   // surrogate region: 16 bytes of 64-bit counters (8-byte aligned for the atomics), then the
   // weights 256 bytes further
   P.off_mlp = off; off = align_up(off + 256 + (size_t)kMlpParams * 4, 256);
@@ -294,6 +302,15 @@ bool plan_aligned(const Plan& P) {
   for (size_t o : offs)
     if (o % 256 != 0) return false;
   return true;
+}
+
+// Launches that take `left` (even) steps, up to kMultiSteps each, from one buffer into the other.
+// In the in-place layout (aa) the second buffer is the read-out area and the state has to end in
+// its own, so their number is even: none for fewer than four steps.
+int64_t multi_launches(bool aa, int64_t left) {
+  const int64_t m = (left + kMultiSteps - 1) / kMultiSteps;
+  if (!aa || m % 2 == 0) return m;
+  return left >= 4 ? m + 1 : 0;
 }
 
 // Layout of the stored state for the read-out kernels: -1 two buffers, else the parity of t.
@@ -455,7 +472,8 @@ int lbm_create(const lbm_params* p, const double* rho0, const double* u0, const 
   }
   c->ws_bytes = P.total;
   c->A = c->ws + P.off_A;
-  c->B = P.aa ? nullptr : c->ws + P.off_B;
+  c->multi = P.multi;
+  c->B = P.aa ? (P.multi ? c->ws + P.off_read : nullptr) : c->ws + P.off_B;
   c->partials = reinterpret_cast<double*>(c->ws + P.off_part);
   c->history = reinterpret_cast<double*>(c->ws + P.off_hist);
   c->readout = reinterpret_cast<double*>(c->ws + P.off_read);
@@ -519,6 +537,22 @@ int lbm_step(lbm_ctx* c, int64_t n) {
   const int de = c->p.diag_every;
   const int64_t hist_before = c->hist_written;
   for (int64_t k = 0; k < n; ++k) {
+    if (c->multi && !(c->aa && (c->t & 1))) {
+      // the steps up to the next diagnostics entry, whose step sums its own moments
+      int64_t ahead = n - k;
+      if (de > 0) ahead = std::min(ahead, de - 1 - c->t % de);
+      int64_t left = ahead & ~(int64_t)1;
+      for (int64_t m = multi_launches(c->aa, left); m > 0; --m) {
+        const int T = (int)(2 * ((left / 2 + m - 1) / m));
+        HIP_TRY(c, launch_bgk_d2q9_multi(c->kind, c->A, c->B, c->L, c->aa, c->omega, c->F, c->p.wall_y != 0, T, c->stream));
+        std::swap(c->A, c->B);
+        c->t += T;
+        k += T;
+        left -= T;
+        c->F_state = c->F;
+      }
+      if (k >= n) break;
+    }
     const int64_t tn = c->t + 1;
     const bool diag = de > 0 && tn % de == 0;
     double* part = diag ? c->partials : nullptr;

@@ -106,6 +106,12 @@ hipError_t launch_bgk_d2q9_aa(int kind, bool odd, void* A, const Layout& L, cons
 hipError_t launch_bgk_d3q27_aa(int kind, bool odd, void* A, const Layout& L, const Grid& G,
                                double omega, const Force& F, bool walls, double* partials,
                                hipStream_t s);
+// `steps` (2, 4 or 6) D2Q9 steps in one launch, from state A to state B. swapped: both states hold
+// population i in slot Q-1-i (the single-buffer state at an even step count).
+constexpr int kMultiSteps = 6;
+hipError_t launch_bgk_d2q9_multi(int kind, const void* A, void* B, const Layout& L, bool swapped,
+                                 double omega, const Force& F, bool walls, int steps,
+                                 hipStream_t s);
 // swap: store population i in slot Q-1-i (single-buffer state at an even step count). With a
 // force the equilibrium is collided once (the stored state is post-collision at t = 0).
 hipError_t launch_init_bgk(int kind, int D, const double* rho, const double* u, void* A,
