@@ -1,0 +1,54 @@
+// Device-to-host copies of read-outs.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstddef>
+#include <cstdint>
+#include <vector>
+
+namespace lbm {
+
+struct HostPiece {
+  void* dst;        // host memory of the caller (pageable)
+  const void* src;  // device memory
+  size_t bytes;
+};
+
+// Copies from the device through pinned staging buffers, several host threads moving them on to
+// the caller's memory. A plain copy to pageable memory runs through one staging path of the
+// runtime on one host thread, which also takes the page faults of newly allocated memory: about
+// 10 GB/s, 20-30% of an output interval. Measured for a whole read-out (moments kernel, totals
+// and copy): 4096^2 D2Q9, 403 MB, 40 -> 10.5 ms; 2048^2, 101 MB, 10 -> 3.2 ms.
+//
+// Each thread alternates between two buffers, the next chunk in flight while it moves the last.
+// Threads x chunk by the bytes of the call, from sweeps of 1-16 threads and 1-8 MiB: above
+// 256 MiB 6 x 4 MiB (403 MB: 10.5 ms; 4 x 2: 11.4, 3 x 4: 12.2, 1 x 4: 29), above 16 MiB 4 x
+// 2 MiB (101 MB: 3.2 ms, the first call 5.7; 6 x 4: 3.1, the first call 7.6, most of it the pinned
+// allocation), above 4 MiB 4 x 1 MiB; below, the plain copy, whose time the threads would not
+// repay. The staging memory belongs to the object, which copies for one caller at a time like
+// the context that owns it.
+class HostCopy {
+ public:
+  HostCopy() = default;
+  HostCopy(const HostCopy&) = delete;
+  HostCopy& operator=(const HostCopy&) = delete;
+  ~HostCopy();
+  // Copies the pieces after the work queued on s; returns when they are in host memory.
+  hipError_t copy(const HostPiece* p, int n, int device, hipStream_t s);
+
+ private:
+  struct Shape {
+    int threads;
+    size_t chunk;
+  };
+  bool reserve(const Shape& sh);
+  void release();
+  hipError_t lane(int w, const Shape& sh, const HostPiece* p, int n, size_t total, int device,
+                  hipStream_t s);
+  char* slab_ = nullptr;  // two chunks per thread
+  size_t slab_bytes_ = 0;
+  std::vector<hipEvent_t> ev_;  // two per thread
+};
+
+}  // namespace lbm

@@ -1,0 +1,109 @@
+#include "host_copy.h"
+
+#include <algorithm>
+#include <cstring>
+#include <thread>
+
+namespace lbm {
+
+HostCopy::~HostCopy() { release(); }
+
+void HostCopy::release() {
+  for (hipEvent_t e : ev_) (void)hipEventDestroy(e);
+  ev_.clear();
+  if (slab_) (void)hipHostFree(slab_);
+  slab_ = nullptr;
+  slab_bytes_ = 0;
+}
+
+bool HostCopy::reserve(const Shape& sh) {
+  const size_t need = 2 * sh.threads * sh.chunk;
+  if (slab_bytes_ < need) {
+    release();
+    void* p = nullptr;
+    if (hipHostMalloc(&p, need, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    slab_ = static_cast<char*>(p);
+    slab_bytes_ = need;
+  }
+  while (ev_.size() < 2 * (size_t)sh.threads) {
+    hipEvent_t e;
+    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    ev_.push_back(e);
+  }
+  return true;
+}
+
+// Chunks w, w + threads, ... of the concatenated pieces.
+hipError_t HostCopy::lane(int w, const Shape& sh, const HostPiece* p, int n, size_t total,
+                          int device, hipStream_t s) {
+  hipError_t e = hipSetDevice(device);  // a thread's current device is its own
+  // fn(piece, offset in it, length, offset in the chunk) for the parts of chunk c
+  auto parts = [&](size_t c, auto&& fn) {
+    const size_t a = c * sh.chunk, b = std::min(total, a + sh.chunk);
+    size_t base = 0;
+    for (int i = 0; i < n; base += p[i++].bytes) {
+      const size_t lo = std::max(a, base), hi = std::min(b, base + p[i].bytes);
+      if (lo < hi) fn(p[i], lo - base, hi - lo, lo - a);
+    }
+  };
+  auto buf = [&](int k) { return slab_ + (2 * w + k) * sh.chunk; };
+  auto fetch = [&](size_t c, int k) {
+    parts(c, [&](const HostPiece& q, size_t off, size_t len, size_t at) {
+      if (e == hipSuccess)
+        e = hipMemcpyAsync(buf(k) + at, static_cast<const char*>(q.src) + off, len,
+                           hipMemcpyDeviceToHost, s);
+    });
+    if (e == hipSuccess) e = hipEventRecord(ev_[2 * w + k], s);
+  };
+  const size_t chunks = (total + sh.chunk - 1) / sh.chunk;
+  int k = 0;
+  if ((size_t)w < chunks && e == hipSuccess) fetch(w, 0);
+  for (size_t c = w; c < chunks && e == hipSuccess; c += sh.threads, k ^= 1) {
+    if (c + sh.threads < chunks) fetch(c + sh.threads, k ^ 1);
+    if (e == hipSuccess) e = hipEventSynchronize(ev_[2 * w + k]);
+    if (e != hipSuccess) break;
+    parts(c, [&](const HostPiece& q, size_t off, size_t len, size_t at) {
+      std::memcpy(static_cast<char*>(q.dst) + off, buf(k) + at, len);
+    });
+  }
+  return e;
+}
+
+hipError_t HostCopy::copy(const HostPiece* p, int n, int device, hipStream_t s) {
+  size_t total = 0;
+  for (int i = 0; i < n; ++i) total += p[i].bytes;
+  const size_t mib = (size_t)1 << 20;
+  const Shape sh = total > 256 * mib ? Shape{6, 4 * mib}
+                                     : Shape{4, total > 16 * mib ? 2 * mib : mib};
+  if (total <= 4 * mib || !reserve(sh)) {
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < n && e == hipSuccess; ++i)
+      e = hipMemcpyAsync(p[i].dst, p[i].src, p[i].bytes, hipMemcpyDeviceToHost, s);
+    const hipError_t es = hipStreamSynchronize(s);
+    return e != hipSuccess ? e : es;
+  }
+  hipError_t res[8];
+  std::thread th[8];
+  int started = 1;  // this thread takes lane 0, and the lanes that get no thread
+  try {
+    for (; started < sh.threads; ++started)
+      th[started] = std::thread([&, w = started] { res[w] = lane(w, sh, p, n, total, device, s); });
+  } catch (...) {
+  }
+  res[0] = lane(0, sh, p, n, total, device, s);
+  for (int w = started; w < sh.threads; ++w) res[w] = lane(w, sh, p, n, total, device, s);
+  for (int w = 1; w < started; ++w) th[w].join();
+  // also after an error: nothing still writes to the staging memory when this returns
+  hipError_t e = hipStreamSynchronize(s);
+  for (int w = 0; w < sh.threads; ++w)
+    if (res[w] != hipSuccess) e = res[w];
+  return e;
+}
+
+}  // namespace lbm

@@ -10,6 +10,7 @@
 #include <string>
 #include <vector>
 
+#include "host_copy.h"
 #include "lbm.h"
 #include "lbm_internal.h"
 
@@ -58,6 +59,8 @@ struct lbm_ctx {
   unsigned long long* mlp_cnt = nullptr;   // {fallbacks, updates}
   bool mlp_set = false;
   double mlp_tol = 0.0;
+  int device = 0;         // device the context was created on
+  HostCopy host_copy;     // staging of large read-outs
   std::string err;
 };
 
@@ -438,6 +441,7 @@ int lbm_create(const lbm_params* p, const double* rho0, const double* u0, const 
       c->dp.full = true;
     }
   }
+  (void)hipGetDevice(&c->device);
   c->L = P.L;
   c->G = P.G;
   c->stream = static_cast<hipStream_t>(p->stream);
@@ -667,10 +671,13 @@ int lbm_moments(lbm_ctx* c, double* rho, double* u, double* T, double* totals) {
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     for (int k = 0; k < kDiagValues; ++k) totals[k] = h[1 + k];
   }
-  if (rho) HIP_TRY(c, hipMemcpyAsync(rho, d_rho, nodes * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  if (u) HIP_TRY(c, hipMemcpyAsync(u, d_u, (size_t)c->D * nodes * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  if (T && c->ddf) HIP_TRY(c, hipMemcpyAsync(T, d_T, nodes * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  HostPiece out[3];
+  int pieces = 0;
+  const size_t field = (size_t)nodes * sizeof(double);
+  if (rho) out[pieces++] = {rho, d_rho, field};
+  if (u) out[pieces++] = {u, d_u, c->D * field};
+  if (T && c->ddf) out[pieces++] = {T, d_T, field};
+  HIP_TRY(c, c->host_copy.copy(out, pieces, c->device, c->stream));
   return LBM_OK;
 }
 
@@ -687,8 +694,8 @@ int lbm_populations(lbm_ctx* c, double* f, double* g) {
       HIP_TRY(c, launch_decode_bgk_red(c->codec, i, c->A, c->L, c->s_dec, c->readout, c->stream));
     else
       HIP_TRY(c, launch_decode_f(c->kind, c->D, i, c->A, c->L, view_of(c), c->p.wall_y != 0, c->readout, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(dst, c->readout, nodes * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    const HostPiece out{dst, c->readout, nodes * sizeof(double)};
+    HIP_TRY(c, c->host_copy.copy(&out, 1, c->device, c->stream));
   }
   return LBM_OK;
 }
