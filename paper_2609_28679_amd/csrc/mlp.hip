@@ -2,8 +2,8 @@
 // D2Q9 stream-collide step, on bfloat16 matrix cores with float32 accumulation. See
 // mlp_common.h for the network, the transposed GEMM formulation and the register layouts.
 //
-// Training of one batch is two launches: k_mlp_grad (forward and backward, one wavefront per
-// 64 samples, per-wavefront partial gradients: the weight gradients are split along the
+// Training of one batch is two launches: k_mlp_grad (forward and backward, one workgroup per
+// 64 samples, per-workgroup partial gradients: the weight gradients are split along the
 // sample dimension, K) and k_mlp_reduce_adam (deterministic sum of the partials in a fixed
 // order, then the Adam update of the float32 master weights).
 #include "mlp_common.h"
@@ -19,240 +19,6 @@ namespace lbm {
 
 constexpr int kPart = kNParam + 1;  // parameters + loss
 
-// ---- forward and backward of one batch -----------------------------------------------------
-// Samples (start + i) mod n for i in [0, B); wavefront w of the grid takes i in [64 w, 64 w + 64).
-__global__ void __launch_bounds__(kBlock)
-k_mlp_grad(const float* __restrict__ X, const float* __restrict__ T, int64_t n, int64_t start,
-           int B, const float* __restrict__ w, float* __restrict__ partials) {
-  __shared__ MlpLds s;
-  __shared__ __attribute__((aligned(16))) short xs[4][64][16];
-  __shared__ float ys[4][64][16];
-  __shared__ __attribute__((aligned(16))) short tA[4][64][64];
-  __shared__ __attribute__((aligned(16))) short tB[4][64][64];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int r = lane & 15, q = lane >> 4;
-  const int gw = blockIdx.x * 4 + wv;  // global wavefront
-  const int i_loc = gw * 64 + lane;
-  const bool valid = i_loc < B;
-  const int64_t idx = (start + (int64_t)(valid ? i_loc : 0)) % n;
-
-  mlp_load_lds(w, s);
-  // inputs (bfloat16, zero padded); invalid samples have zero input and zero gradient
-#pragma unroll
-  for (int k = 0; k < 16; ++k)
-    xs[wv][lane][k] = (valid && k < kIn) ? f2bf(X[idx * kIn + k]) : (short)0;
-  __syncthreads();
-
-  MlpAct a;
-  mlp_forward_wave(s, xs[wv], a, true);
-  // outputs to per-sample rows
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) ys[wv][16 * nt + r][4 * q + j] = a.y[nt][j];
-  // H2^T rows [hidden][sample] for dW3
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) tB[wv][16 * m + 4 * q + j][16 * nt + r] = a.h2[m][nt][j];
-  __syncthreads();
-
-  // ---- loss and output gradient (lane = sample) ----------------------------------------
-  float y[9], dy[9];
-#pragma unroll
-  for (int i = 0; i < 9; ++i) y[i] = ys[wv][lane][i];
-  project9(y);
-  float loss = 0.0f;
-  const float scale = 2.0f / ((float)B * 9.0f);
-#pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    const float d = valid ? y[i] - T[idx * kOut + i] : 0.0f;
-    loss += d * d;
-    dy[i] = scale * d;
-  }
-  project9(dy);  // the projection is symmetric: dL/dy = P dL/dyhat
-#pragma unroll
-  for (int o = 0; o < 16; ++o) tA[wv][o][lane] = o < 9 ? f2bf(dy[o]) : (short)0;
-  __syncthreads();
-
-  float* out = partials + (int64_t)gw * kPart;
-  // db3 and the loss: wavefront sums (fixed shuffle tree)
-#pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    const float v = (float)wave_sum((double)dy[i]);
-    if (lane == 0) out[oB3 + i] = v;
-  }
-  {
-    const float v = (float)wave_sum((double)loss);
-    if (lane == 0) out[kNParam] = v / ((float)B * 9.0f);
-  }
-  // dW3[o][h] = sum_s dy[s][o] h2[s][h]: A = dY^T (rows o), B = H2 (cols h), K = samples
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int kt = 0; kt < 4; ++kt)
-      acc = mfma16(ld4(&tA[wv][r][16 * kt + 4 * q]), ld4(&tB[wv][16 * nt + r][16 * kt + 4 * q]), acc);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (4 * q + j < kOut) out[oW3 + (4 * q + j) * kHid + 16 * nt + r] = acc[j];
-  }
-  // dH2^T = W3^T dY^T, then dZ2 = dH2 gelu'(Z2)
-  bf16x4 dz2[4][4];
-  float db2[4][4];
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    bf16x4 wa;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) wa[j] = s.w3[4 * q + j][16 * m + r];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) db2[m][j] = 0.0f;
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      bf16x4 bb;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bb[j] = tA[wv][4 * q + j][16 * nt + r];
-      f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-      acc = mfma16(wa, bb, acc);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float g, dg;
-        gelu_and_grad(a.z2[m][nt][j], g, dg);
-        const float d = acc[j] * dg;
-        db2[m][j] += d;
-        dz2[m][nt][j] = f2bf(d);
-      }
-    }
-  }
-  __syncthreads();  // tA (dY^T) and tB (H2^T) are free again
-  // dZ2 rows [out][sample] into tA, H1^T rows [hidden][sample] into tB
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        tA[wv][16 * m + 4 * q + j][16 * nt + r] = dz2[m][nt][j];
-        tB[wv][16 * m + 4 * q + j][16 * nt + r] = a.h1[m][nt][j];
-      }
-  // db2: sum over the 16 lanes that share q (samples r)
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float v = db2[m][j];
-      v += __shfl_xor(v, 8, 64);
-      v += __shfl_xor(v, 4, 64);
-      v += __shfl_xor(v, 2, 64);
-      v += __shfl_xor(v, 1, 64);
-      if (r == 0) out[oB2 + 16 * m + 4 * q + j] = v;
-    }
-  __syncthreads();
-  // dW2 = dZ2^T H1
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int kt = 0; kt < 4; ++kt)
-        acc = mfma16(ld4(&tA[wv][16 * m + r][16 * kt + 4 * q]), ld4(&tB[wv][16 * nt + r][16 * kt + 4 * q]), acc);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) out[oW2 + (16 * m + 4 * q + j) * kHid + 16 * nt + r] = acc[j];
-    }
-  // dH1^T = W2^T dZ2^T, dZ1 = dH1 gelu'(Z1)
-  bf16x4 dz1[4][4];
-  float db1[4][4];
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    bf16x4 wa[4];
-#pragma unroll
-    for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) wa[kt][j] = s.w2[16 * kt + 4 * q + j][16 * m + r];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) db1[m][j] = 0.0f;
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int kt = 0; kt < 4; ++kt) acc = mfma16(wa[kt], dz2[kt][nt], acc);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float g, dg;
-        gelu_and_grad(a.z1[m][nt][j], g, dg);
-        const float d = acc[j] * dg;
-        db1[m][j] += d;
-        dz1[m][nt][j] = f2bf(d);
-      }
-    }
-  }
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float v = db1[m][j];
-      v += __shfl_xor(v, 8, 64);
-      v += __shfl_xor(v, 4, 64);
-      v += __shfl_xor(v, 2, 64);
-      v += __shfl_xor(v, 1, 64);
-      if (r == 0) out[oB1 + 16 * m + 4 * q + j] = v;
-    }
-  __syncthreads();  // tA, tB free
-  // dZ1 rows [out][sample] into tA, X^T rows [feature][sample] into tB
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) tA[wv][16 * m + 4 * q + j][16 * nt + r] = dz1[m][nt][j];
-#pragma unroll
-  for (int k = 0; k < 16; ++k) tB[wv][k][lane] = xs[wv][lane][k];
-  __syncthreads();
-  // dW1 = dZ1^T X (features 0..11 of 16)
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int kt = 0; kt < 4; ++kt)
-      acc = mfma16(ld4(&tA[wv][16 * m + r][16 * kt + 4 * q]), ld4(&tB[wv][r][16 * kt + 4 * q]), acc);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (r < kIn) out[oW1 + (16 * m + 4 * q + j) * kIn + r] = acc[j];
-  }
-}
-
-// Sum of the per-wavefront partials in wavefront order; optional gradient output and Adam step.
-__global__ void k_mlp_reduce_adam(const float* __restrict__ partials, int nw, float* __restrict__ grad,
-                                  float* __restrict__ loss, float* __restrict__ w, float* __restrict__ m,
-                                  float* __restrict__ v, int adam, float lr, float b1, float b2,
-                                  float eps, float c1, float c2) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p > kNParam) return;
-  float g = 0.0f;
-  for (int k = 0; k < nw; ++k) g += partials[(int64_t)k * kPart + p];
-  if (p == kNParam) {
-    if (loss) *loss = g;
-    return;
-  }
-  if (grad) grad[p] = g;
-  if (adam) {
-    const float mm = b1 * m[p] + (1.0f - b1) * g;
-    const float vv = b2 * v[p] + (1.0f - b2) * g * g;
-    m[p] = mm;
-    v[p] = vv;
-    // bias-corrected moments: c1 = 1 - b1^t, c2 = 1 - b2^t
-    w[p] -= lr * (mm / c1) / (sqrtf(vv / c2) + eps);
-  }
-}
-
-// Per-wave LDS rows of the inference kernels: a sample's 12 bfloat16 inputs (zero padded to
-// 24) and, once its tile has been evaluated, the same row's 12 float32 outputs (9 used). The
-// outputs of tile n overwrite the inputs of tile n only, which that tile has already read.
-constexpr int kIoS = 12;  // floats per row (48 bytes)
-
 // Orders this wave's LDS writes before other lanes of the same wave read them: LDS operations
 // of one wave execute in order, so only the compiler has to be kept from moving memory
 // operations across this point (no workgroup barrier).
@@ -262,12 +28,375 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Network of the four tiles of one wave: inputs in io rows (bfloat16), outputs back into the
-// same rows (float32, C layout scattered to rows).
-__device__ __forceinline__ void mlp_wave_tiles(const MlpLdsP& s, float (*io)[kIoS]) {
+// ---- forward and backward of one batch -----------------------------------------------------
+// LDS of one workgroup: weights (bfloat16, also transposed for the backward products) and biases,
+// and the [feature][sample] operands of the weight gradients. Rows of 20 and 68 elements start on
+// distinct LDS banks. dL/dZ is kept as its two factors dL/dH and dH/dZ: the biases' gradients sum
+// the products with one rounding each (fma), the weight gradients round them to bfloat16. What
+// the forward pass alone uses makes room for one of them.
+struct __attribute__((aligned(16))) GradForward {
+  float b1[kHid], b2[kHid], b3[16];
+  short w1[kHid][kW1S], w2[kHid][kW2S], w3[16][kW2S];
+  short x[64][kW1S];  // inputs [sample][feature]
+};
+struct __attribute__((aligned(16))) GradLds {
+  union {
+    GradForward f;
+    float g2[kHid][kW2S];  // dL/dH2^T
+  };
+  float s2[kHid][kW2S];                    // dH2/dZ2^T
+  float g1[kHid][kW2S], s1[kHid][kW2S];  // dL/dH1^T, dH1/dZ1^T
+  short w2t[kHid][kW2S], w3t[kHid][kW1S];
+  short xt[16][kW2S], dy[16][kW2S];  // X^T, dL/dY^T
+  short h1[kHid][kW2S], h2[kHid][kW2S];
+  float y[64][20];
+  double db3[4][16], loss[4];  // per wavefront
+};
+static_assert(sizeof(GradLds) <= 160 * 1024, "the LDS of a compute unit");
+
+// Sum over the 16 lanes of a row, in every lane: four rotations within the row, which the vector
+// unit reads directly (a shuffle through LDS costs its latency each time).
+template <int N>
+__device__ __forceinline__ int row_rotate(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, 0x120 + N, 0xf, 0xf, false);
+}
+template <int N>
+__device__ __forceinline__ float row_rotate(float v) {
+  return __int_as_float(row_rotate<N>(__float_as_int(v)));
+}
+template <int N>
+__device__ __forceinline__ double row_rotate(double v) {
+  return __hiloint2double(row_rotate<N>(__double2hiint(v)), row_rotate<N>(__double2loint(v)));
+}
+template <typename R>
+__device__ __forceinline__ R row_sum(R v) {
+  v += row_rotate<8>(v);
+  v += row_rotate<4>(v);
+  v += row_rotate<2>(v);
+  v += row_rotate<1>(v);
+  return v;
+}
+
+__device__ __forceinline__ float add_rounded(float sum, float a, float b) {
+#pragma clang fp contract(off)
+  return sum + a * b;
+}
+
+// One workgroup of four wavefronts takes the samples (start + i) mod n, i in [64 b, 64 b + 64),
+// and writes one row of partial gradients and loss: the weight gradients are split along the
+// sample dimension (K). Wavefront v runs the forward and backward passes of samples 16 v ..
+// 16 v + 15 (one tile column: a quarter of the matrix and GELU work of 64 samples) and leaves the
+// activations and gradients transposed in LDS; after one barrier it forms the weight gradients
+// of row tile v over all 64 samples. A batch is bound by latency, not by rate (4096 samples are
+// 64 workgroups, and the serial chain of one wavefront is what a step takes): with one wavefront
+// for all of its 64 samples and four such wavefronts per compute unit, a training step (this
+// kernel and the next) took 44.7 us at 64 samples, 58.5 at 4096 and 289 at 65536; it takes 12.7,
+// 13.2 and 51.
+__global__ void __launch_bounds__(kBlock)
+k_mlp_grad(const float* __restrict__ X, const float* __restrict__ T, int64_t n, int64_t start,
+           int B, const float* __restrict__ w, float* __restrict__ partials) {
+  __shared__ GradLds s;
+  const int t = threadIdx.x;
+  const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int r = lane & 15, q = lane >> 4;
+  const int first = blockIdx.x * 64;
+  // sample k of this workgroup; past the batch: its first one, with zero input and gradient
+  auto sample = [&](int k) {
+    int64_t i = start + (first + k < B ? first + k : 0);
+    if (i >= n) i -= n;
+    return i >= n ? i % n : i;
+  };
+
+  // weights and inputs into LDS, every load issued before the first write
+  {
+    float a1[3], a2[16], a3[3], xv[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int e = t + k * kBlock;
+      xv[k] = first + e / kIn < B ? X[sample(e / kIn) * kIn + e % kIn] : 0.0f;
+      a1[k] = w[oW1 + e];
+      a3[k] = e < kOut * kHid ? w[oW3 + e] : 0.0f;
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) a2[k] = w[oW2 + t + k * kBlock];
+    const float b = t < kHid ? w[oB1 + t]
+                             : (t < 2 * kHid ? w[oB2 + t - kHid]
+                                             : (t < 2 * kHid + kOut ? w[oB3 + t - 2 * kHid] : 0.0f));
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int e = t + k * kBlock;
+      s.f.w1[e / kIn][e % kIn] = f2bf(a1[k]);
+      const short xb = f2bf(xv[k]);
+      s.f.x[e / kIn][e % kIn] = xb;
+      s.xt[e % kIn][e / kIn] = xb;
+      const short wb = f2bf(a3[k]);  // rows 9..11: zero
+      s.f.w3[e / kHid][e % kHid] = wb;
+      s.w3t[e % kHid][e / kHid] = wb;
+    }
+    // zero padding: inputs 12..15, outputs 12..15
+    s.f.w1[t / 4][kIn + t % 4] = 0;
+    s.f.x[t / 4][kIn + t % 4] = 0;
+    s.w3t[t / 4][12 + t % 4] = 0;
+    s.xt[kIn + t / 64][t % 64] = 0;
+    s.f.w3[12 + t / 64][t % 64] = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int e = t + k * kBlock;
+      const short v = f2bf(a2[k]);
+      s.f.w2[e / kHid][e % kHid] = v;
+      s.w2t[e % kHid][e / kHid] = v;
+    }
+    if (t < kHid) s.f.b1[t] = b;
+    else if (t < 2 * kHid) s.f.b2[t - kHid] = b;
+    else if (t < 2 * kHid + 16) s.f.b3[t - 2 * kHid] = b;
+  }
+  __syncthreads();
+
+  const int c = 16 * wv + r;  // this lane's sample
+  const bool valid = first + c < B;
+  const int64_t idx = sample(c);
+  float target[9];
+#pragma unroll
+  for (int i = 0; i < 9; ++i) target[i] = T[idx * kOut + i];
+
+  // ---- forward ---------------------------------------------------------------------------
+  f32x4 z1[4], z2[4];
+  bf16x4 h1[4];
+  {
+    const bf16x4 xb = ld4(&s.f.x[c][4 * q]);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      z1[m] = mfma16(ld4(&s.f.w1[16 * m + r][4 * q]), xb, bias4(s.f.b1 + 16 * m, lane));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        h1[m][j] = f2bf(gelu(z1[m][j]));
+        s.h1[16 * m + 4 * q + j][c] = h1[m][j];
+      }
+    }
+    bf16x4 h2[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      f32x4 acc = bias4(s.f.b2 + 16 * m, lane);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc = mfma16(ld4(&s.f.w2[16 * m + r][16 * k + 4 * q]), h1[k], acc);
+      z2[m] = acc;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        h2[m][j] = f2bf(gelu(acc[j]));
+        s.h2[16 * m + 4 * q + j][c] = h2[m][j];
+      }
+    }
+    f32x4 y = bias4(s.f.b3, lane);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) y = mfma16(ld4(&s.f.w3[r][16 * k + 4 * q]), h2[k], y);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s.y[c][4 * q + j] = y[j];
+  }
+  // the outputs of a sample come from its four lanes; g2 takes the place of the forward weights
+  __syncthreads();
+
+  // ---- loss and output gradient: every lane of a sample forms all nine, lane q takes 4 q + j --
+  bf16x4 dyb;
+  {
+    float y[9], d[9], dy[9], loss = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) y[i] = s.y[c][i];
+    project9_outputs(y);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      d[i] = valid ? y[i] - target[i] : 0.0f;
+      loss += d[i] * d[i];
+    }
+    // the projection is symmetric: dL/dy = P dL/dyhat
+    project9_gradient(d, 2.0f / ((float)B * 9.0f), dy);
+    const double l = row_sum((double)loss);
+    if (lane == 0) s.loss[wv] = l;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float e = q == 0 ? dy[j] : (q == 1 ? dy[4 + j] : (q == 2 && j == 0 ? dy[8] : 0.0f));
+      dyb[j] = f2bf(e);
+      s.dy[4 * q + j][c] = dyb[j];
+      const double v = row_sum((double)e);
+      if (r == 0) s.db3[wv][4 * q + j] = v;
+    }
+  }
+
+  // ---- backward: dH2^T = W3^T dY^T, dZ2 = dH2 gelu'(Z2); dH1^T = W2^T dZ2^T, dZ1 likewise ------
+  auto backward = [&](const f32x4& dh, const f32x4& z, float (*gt)[kW2S], float (*st)[kW2S], int m) {
+    bf16x4 dz;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float slope = gelu_derivative(z[j]);
+      dz[j] = f2bf(dh[j] * slope);
+      gt[16 * m + 4 * q + j][c] = dh[j];
+      st[16 * m + 4 * q + j][c] = slope;
+    }
+    return dz;
+  };
+  bf16x4 dz2[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    dz2[m] = backward(mfma16(ld4(&s.w3t[16 * m + r][4 * q]), dyb, zero), z2[m], s.g2, s.s2, m);
+  }
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc = mfma16(ld4(&s.w2t[16 * m + r][16 * k + 4 * q]), dz2[k], acc);
+    backward(acc, z1[m], s.g1, s.s1, m);
+  }
+  __syncthreads();
+
+  // ---- weight gradients over the 64 samples: row tile wv of W1 and W2, column tile wv of W3 -----
+  float* out = partials + (int64_t)blockIdx.x * kPart;
+  typedef bf16x4 Rows[4];  // one operand row over the 64 samples
+  auto operand = [&](const short* row, Rows& o) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o[k] = ld4(row + 16 * k + 4 * q);
+  };
+  auto rounded = [&](const float* g, const float* slope, Rows& o) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const f32x4 a = *reinterpret_cast<const f32x4*>(g + 16 * k + 4 * q);
+      const f32x4 b = *reinterpret_cast<const f32x4*>(slope + 16 * k + 4 * q);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[k][j] = f2bf(a[j] * b[j]);
+    }
+  };
+  auto product = [&](const Rows& a, const Rows& b) {
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc = mfma16(a[k], b[k], acc);
+    return acc;
+  };
+  Rows za, hb;
+  rounded(s.g2[16 * wv + r], s.s2[16 * wv + r], za);
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) {
+    operand(s.h1[16 * nt + r], hb);
+    const f32x4 d = product(za, hb);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) out[oW2 + (16 * wv + 4 * q + j) * kHid + 16 * nt + r] = d[j];
+  }
+  rounded(s.g1[16 * wv + r], s.s1[16 * wv + r], za);
+  operand(s.xt[r], hb);
+  const f32x4 d1 = product(za, hb);
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (r < kIn) out[oW1 + (16 * wv + 4 * q + j) * kIn + r] = d1[j];
+  operand(s.dy[r], za);
+  operand(s.h2[16 * wv + r], hb);
+  const f32x4 d3 = product(za, hb);
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (4 * q + j < kOut) out[oW3 + (4 * q + j) * kHid + 16 * wv + r] = d3[j];
+  // biases: samples 16 apart added in order, then over the 16 lanes of a row. Which products are
+  // rounded before they are added follows the trainings this kernel has to reproduce (see
+  // gelu_derivative); either choice is within an ulp of the other.
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int h = 16 * wv + 4 * q + j;
+    float v1 = 0.0f, v2 = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      v1 = __builtin_fmaf(s.g1[h][16 * k + r], s.s1[h][16 * k + r], v1);
+      const float g = s.g2[h][16 * k + r], slope = s.s2[h][16 * k + r];
+      v2 = wv == 0 && j == 0 ? __builtin_fmaf(g, slope, v2) : add_rounded(v2, g, slope);
+    }
+    v1 = row_sum(v1);
+    v2 = row_sum(v2);
+    if (r == 0) {
+      out[oB1 + h] = v1;
+      out[oB2 + h] = v2;
+    }
+  }
+  if (t < kOut)
+    out[oB3 + t] = (float)(((s.db3[0][t] + s.db3[1][t]) + s.db3[2][t]) + s.db3[3][t]);
+  else if (t == kBlock - 1)
+    out[kNParam] = (float)(((s.loss[0] + s.loss[1]) + s.loss[2]) + s.loss[3]) / ((float)B * 9.0f);
+}
+
+// Sum of the partials in row order; optional gradient output and Adam step. A workgroup takes 64
+// parameters. Its wavefronts bring kReduceRows rows at a time into LDS, the next ones on their way
+// while the first wavefront adds the last ones up: the order of the sum is that of one thread
+// reading row after row, which took 16 us for the 64 rows of 4096 samples (22 workgroups, each
+// load waited for in small groups).
+constexpr int kReduceWaves = 16, kReduceRows = 8 * kReduceWaves;
+__global__ void __launch_bounds__(64 * kReduceWaves)
+k_mlp_reduce_adam(const float* __restrict__ partials, int nw, float* __restrict__ grad,
+                  float* __restrict__ loss, float* __restrict__ w, float* __restrict__ m,
+                  float* __restrict__ v, int adam, float lr, float b1, float b2, float eps,
+                  float c1, float c2) {
+  __shared__ float part[2][kReduceRows][64];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int p = blockIdx.x * 64 + lane;
+  const float* col = partials + min(p, kNParam);
+  // the parameter and its moments are on their way while the rows are summed
+  const bool update = adam && wv == 0 && p < kNParam;
+  const float w0 = update ? w[p] : 0.0f, m0 = update ? m[p] : 0.0f, v0 = update ? v[p] : 0.0f;
+  float a[8];
+  auto fetch = [&](int k0) {  // rows past the last one are read as zero
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int k = k0 + i * kReduceWaves + wv;
+      a[i] = k < nw ? col[(int64_t)k * kPart] : 0.0f;
+    }
+  };
+  fetch(0);
+  float g = 0.0f;
+  for (int k0 = 0, b = 0; k0 < nw; k0 += kReduceRows, b ^= 1) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) part[b][i * kReduceWaves + wv][lane] = a[i];
+    if (k0 + kReduceRows < nw) fetch(k0 + kReduceRows);
+    __syncthreads();
+    if (wv == 0) {
+      const int n = min(kReduceRows, nw - k0);
+      for (int k = 0; k < n; k += 16) {  // rows past nw hold zero
+        float r[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) r[i] = part[b][k + i][lane];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) g += r[i];
+      }
+    }
+  }
+  if (wv != 0 || p > kNParam) return;
+  if (p == kNParam) {
+    if (loss) *loss = g;
+    return;
+  }
+  if (grad) grad[p] = g;
+  if (adam) {
+    const float mm = __builtin_fmaf(1.0f - b1, g, b1 * m0);
+    const float vv = __builtin_fmaf((1.0f - b2) * g, g, b2 * v0);
+    m[p] = mm;
+    v[p] = vv;
+    // bias-corrected moments: c1 = 1 - b1^t, c2 = 1 - b2^t
+    w[p] = w0 - lr * (mm / c1) / (sqrtf(vv / c2) + eps);
+  }
+}
+
+// Per-wave LDS rows of the inference kernels: a sample's 12 bfloat16 inputs (zero padded to
+// 24) and, once its tile has been evaluated, the same row's 12 float32 outputs (9 used). The
+// outputs of tile n overwrite the inputs of tile n only, which that tile has already read.
+constexpr int kIoS = 12;  // floats per row (48 bytes)
+
+// Network of one tile (16 samples) of the 64 io rows: inputs in the rows (bfloat16), outputs back
+// into the same rows (float32, C layout scattered to rows).
+__device__ __forceinline__ void mlp_io_tile(const MlpLdsP& s, float (*io)[kIoS], int nt) {
   const int lane = threadIdx.x & 63;
   const int r = lane & 15, q = lane >> 4;
   const short(*xs)[2 * kIoS] = reinterpret_cast<const short(*)[2 * kIoS]>(io);
+  const f32x4 yt = mlp_forward_tile32<2 * kIoS>(s, xs, nt);
+  if (q < 3) {  // output rows 0..11 (9 used)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) io[16 * nt + r][4 * q + j] = yt[j];
+  }
+}
+
+// Network of the four tiles of one wave.
+__device__ __forceinline__ void mlp_wave_tiles(const MlpLdsP& s, float (*io)[kIoS]) {
 #pragma unroll 1
   for (int nt = 0; nt < 4; ++nt) {
     // The weights are re-read from LDS for every tile instead of being hoisted into registers
@@ -278,11 +407,7 @@ __device__ __forceinline__ void mlp_wave_tiles(const MlpLdsP& s, float (*io)[kIo
     int z = 0;
     asm volatile("" : "+v"(z));
     const MlpLdsP& sz = *reinterpret_cast<const MlpLdsP*>(reinterpret_cast<const char*>(&s) + z);
-    const f32x4 yt = mlp_forward_tile32<2 * kIoS>(sz, xs, nt);
-    if (q < 3) {  // output rows 0..11 (9 used)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) io[16 * nt + r][4 * q + j] = yt[j];
-    }
+    mlp_io_tile(sz, io, nt);
   }
 }
 
@@ -300,25 +425,37 @@ __device__ __forceinline__ void put_inputs(float* row, const float (&xf)[kIn], b
   r[1] = u32x4{w[4], w[5], 0u, 0u};
 }
 
-// Forward pass for n samples (projected outputs), on the inference tiles.
+// Forward pass for n samples (projected outputs), on the inference tiles. SPREAD: one workgroup
+// per 64 samples, each wavefront one tile of them, else 64 samples (four tiles) per wavefront.
+template <bool SPREAD>
 __global__ void __launch_bounds__(kBlock)
 k_mlp_forward(const float* __restrict__ X, int64_t n, const float* __restrict__ w, float* __restrict__ Y) {
   __shared__ MlpLdsP s;
-  __shared__ __attribute__((aligned(16))) float io[4][64][kIoS];
+  __shared__ __attribute__((aligned(16))) float io[SPREAD ? 1 : 4][64][kIoS];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t i = ((int64_t)blockIdx.x * 4 + wv) * 64 + lane;
+  const bool mine = !SPREAD || wv == 0;  // this wavefront moves inputs and outputs
+  const int rows = SPREAD ? 0 : wv;
+  const int64_t i = ((int64_t)blockIdx.x * (SPREAD ? 1 : 4) + rows) * 64 + lane;
   const bool valid = i < n;
-  mlp_load_lds_vec(w, s);
-  float xf[kIn];
+  if (mine) {
+    float xf[kIn];
 #pragma unroll
-  for (int k = 0; k < kIn; ++k) xf[k] = valid ? X[i * kIn + k] : 0.0f;
-  put_inputs(io[wv][lane], xf, valid);
+    for (int k = 0; k < kIn; ++k) xf[k] = valid ? X[i * kIn + k] : 0.0f;
+    put_inputs(io[rows][lane], xf, valid);
+  }
+  mlp_load_lds_vec(w, s);
   __syncthreads();  // the weights
-  mlp_wave_tiles(s, io[wv]);
-  wave_lds_sync();
+  if (SPREAD) {
+    mlp_io_tile(s, io[0], wv);
+    __syncthreads();
+  } else {
+    mlp_wave_tiles(s, io[wv]);
+    wave_lds_sync();
+  }
+  if (!mine) return;
   float y[9];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) y[k] = io[wv][lane][k];
+  for (int k = 0; k < 9; ++k) y[k] = io[rows][lane][k];
   project9(y);
   if (valid)
 #pragma unroll
@@ -562,25 +699,33 @@ k_bgk_d2q9_mlp(const float* __restrict__ A, float* __restrict__ B, int nx, int n
 hipError_t launch_mlp_grad(const float* X, const float* T, int64_t n, int64_t start, int B,
                            const float* w, float* partials, hipStream_t s) {
   const int nw = (B + 63) / 64;
-  k_mlp_grad<<<(nw + 3) / 4, kBlock, 0, s>>>(X, T, n, start, B, w, partials);
+  k_mlp_grad<<<nw, kBlock, 0, s>>>(X, T, n, start, B, w, partials);
   return hipGetLastError();
 }
 
-int mlp_partial_count(int B) { return (((B + 63) / 64) + 3) / 4 * 4; }
+int mlp_partial_count(int B) { return (B + 63) / 64; }
 
 hipError_t launch_mlp_reduce_adam(const float* partials, int nw, float* grad, float* loss, float* w,
                                   float* m, float* v, bool adam, float lr, int64_t t, hipStream_t s) {
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
   const float c1 = (float)(1.0 - std::pow(0.9, (double)t));
   const float c2 = (float)(1.0 - std::pow(0.999, (double)t));
-  k_mlp_reduce_adam<<<(kNParam + 1 + kBlock - 1) / kBlock, kBlock, 0, s>>>(
+  k_mlp_reduce_adam<<<(kNParam + 64) / 64, 64 * kReduceWaves, 0, s>>>(
       partials, nw, grad, loss, w, m, v, adam ? 1 : 0, lr, b1, b2, eps, c1, c2);
   return hipGetLastError();
 }
 
+// Workgroups of 64 samples up to 2^18 samples, 64 samples per wavefront above (us, one tile / four
+// tiles per wavefront: 64 samples 4.0 / 6.8, 4096 4.3 / 7.2, 65536 6.7 / 7.8, 2^18 19.5 / 20.7,
+// 2^20 65.8 / 61.9, 2^22 259 / 218): few workgroups are bound by one wavefront's chain of four
+// tiles, many by the loads of the weights, which a workgroup of 256 samples shares.
+constexpr int64_t kSpreadForward = 4096;
 hipError_t launch_mlp_forward(const float* X, int64_t n, const float* w, float* Y, hipStream_t s) {
   const int64_t nw = (n + 63) / 64;
-  k_mlp_forward<<<(unsigned)((nw + 3) / 4), kBlock, 0, s>>>(X, n, w, Y);
+  if (nw <= kSpreadForward)
+    k_mlp_forward<true><<<(unsigned)nw, kBlock, 0, s>>>(X, n, w, Y);
+  else
+    k_mlp_forward<false><<<(unsigned)((nw + 3) / 4), kBlock, 0, s>>>(X, n, w, Y);
   return hipGetLastError();
 }
 
@@ -649,15 +794,15 @@ hipError_t launch_bgk_d2q9_mlp(const void* A, void* B, const Layout& L, const Gr
 }
 
 // ---- gradient without allocation ---------------------------------------------------------------
-// For callers that cannot call hipMalloc (graph capture, serving loops): the per-wavefront
-// partial gradients of k_mlp_grad go to a fixed device array instead of a trainer buffer. Each
+// For callers that cannot call hipMalloc (graph capture, serving loops): the partial
+// gradients of k_mlp_grad go to a fixed device array instead of a trainer buffer. Each
 // GPU the library runs on holds its own copy of the array until the process ends; its device
 // address is looked up once per device (with that device current) and kept. k_mlp_grad writes
 // every entry of the rows it uses, so nothing has to be cleared between calls; calls that
 // overlap on one GPU race on the array.
 namespace {
 constexpr int kStaticMaxSamples = LBM_MLP_STATIC_MAX_SAMPLES;
-constexpr int kStaticRows = ((kStaticMaxSamples + 63) / 64 + 3) / 4 * 4;
+constexpr int kStaticRows = (kStaticMaxSamples + 63) / 64;
 static __device__ __align__(256) float scratch[(size_t)kStaticRows * kPart];
 
 constexpr int kMaxDevices = 64;

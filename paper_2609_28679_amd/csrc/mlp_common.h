@@ -50,15 +50,28 @@ __device__ __forceinline__ bf16x8 cat8(bf16x4 lo, bf16x4 hi) {
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// GELU, tanh form (Hendrycks and Gimpel 2016), and its derivative, in float32;
-// tanh(t) = 1 - 2 / (1 + exp(2 t)).
-__device__ __forceinline__ void gelu_and_grad(float z, float& g, float& dg) {
+// 2 / d for d >= 1 as the division rounds it, without its range scaling: the hardware reciprocal
+// with a Newton step, then two residual corrections of the quotient.
+__device__ __forceinline__ float two_over(float d) {
+  float inv = __builtin_amdgcn_rcpf(d);
+  inv = __builtin_fmaf(__builtin_fmaf(-d, inv, 1.0f), inv, inv);
+  float h = 2.0f * inv;
+  h = __builtin_fmaf(__builtin_fmaf(-d, h, 2.0f), inv, h);
+  return __builtin_fmaf(__builtin_fmaf(-d, h, 2.0f), inv, h);
+}
+
+// Training: the derivative of the GELU (tanh form, Hendrycks and Gimpel 2016) in float32, with
+// tanh(t) = 1 - 2 / (1 + exp(2 t)). Beyond 2 t = 80 the quotient is far below half an ulp of 1;
+// the bound keeps its steps finite. The roundings of this function and of the two projections
+// below are written out (no contraction left to the compiler): Adam divides by the gradient's
+// own size, so another rounding of one gradient is a visibly different network 200 steps on.
+__device__ __forceinline__ float gelu_derivative(float z) {
+#pragma clang fp contract(off)
   const float k = 0.7978845608028654f, a = 0.044715f;
-  const float t = k * (z + a * z * z * z);
-  const float e = __expf(2.0f * t);
-  const float th = 1.0f - 2.0f / (1.0f + e);
-  g = 0.5f * z * (1.0f + th);
-  dg = 0.5f * (1.0f + th) + 0.5f * z * (1.0f - th * th) * k * (1.0f + 3.0f * a * z * z);
+  const float t = k * __builtin_fmaf(z, z * (a * z), z);
+  const float th = 1.0f - two_over(1.0f + __expf(fminf(t + t, 80.0f)));
+  const float slope = k * ((0.5f * z) * __builtin_fmaf(-th, th, 1.0f));
+  return __builtin_fmaf(0.5f, 1.0f + th, __builtin_fmaf(z, (3.0f * a) * z, 1.0f) * slope);
 }
 // Forward-only form: (1 + tanh t)/2 = 1/(1 + exp(-2t)), so gelu(z) = z / (1 + 2^(z (c0 + c1 z^2)))
 // with c0 = -2 k log2(e), c1 = -2 k a log2(e): five VALU operations, one hardware 2^x and one
@@ -70,15 +83,7 @@ __device__ __forceinline__ float gelu(float z) {
   return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
 }
 
-// Shared weights of one workgroup (bfloat16, zero padded) and biases (float32).
-struct __attribute__((aligned(16))) MlpLds {
-  short w1[kHid][16];    // W1 padded to 16 inputs
-  short w2[kHid][kHid];
-  short w3[16][kHid];    // W3 padded to 16 outputs
-  float b1[kHid], b2[kHid], b3[16];
-};
-
-// The same weights for the inference tiles, rows padded (W1 to 20, W2 and W3 to 68 bfloat16)
+// Weights of one workgroup for the inference tiles (bfloat16, zero padded), rows padded (W1 to 20, W2 and W3 to 68 bfloat16)
 // so that the 16 rows one operand read touches start on distinct LDS banks.
 constexpr int kW1S = 20, kW2S = 68;
 struct __attribute__((aligned(16))) MlpLdsP {
@@ -130,26 +135,6 @@ __device__ __forceinline__ void mlp_load_lds_vec(const float* __restrict__ w, Ml
   else if (t < 2 * kHid + 16) s.b3[t - 2 * kHid] = 0.0f;
 }
 
-// Cooperative load of the float32 blob into LDS (rounded to bfloat16); either weight layout.
-template <class Lds>
-__device__ __forceinline__ void mlp_load_lds(const float* __restrict__ w, Lds& s) {
-  for (int k = threadIdx.x; k < kHid * 16; k += blockDim.x) {
-    const int o = k / 16, i = k % 16;
-    s.w1[o][i] = i < kIn ? f2bf(w[oW1 + o * kIn + i]) : (short)0;
-  }
-  for (int k = threadIdx.x; k < kHid * kHid; k += blockDim.x)
-    s.w2[k / kHid][k % kHid] = f2bf(w[oW2 + k]);
-  for (int k = threadIdx.x; k < 16 * kHid; k += blockDim.x) {
-    const int o = k / kHid, i = k % kHid;
-    s.w3[o][i] = o < kOut ? f2bf(w[oW3 + o * kHid + i]) : (short)0;
-  }
-  for (int k = threadIdx.x; k < kHid; k += blockDim.x) {
-    s.b1[k] = w[oB1 + k];
-    s.b2[k] = w[oB2 + k];
-  }
-  for (int k = threadIdx.x; k < 16; k += blockDim.x) s.b3[k] = k < kOut ? w[oB3 + k] : 0.0f;
-}
-
 // Four consecutive bfloat16 values from LDS; p is 8-byte aligned at every call site (rows of
 // 16, 20, 24, 64 or 68 elements, column offsets multiples of 4, arrays 16-byte aligned), which lets the
 // compiler emit one ds_read_b64 with an immediate offset instead of a per-load address register.
@@ -161,90 +146,6 @@ __device__ __forceinline__ bf16x4 ld4(const short* p) {
 // where two-word reads would need an address add each)
 __device__ __forceinline__ f32x4 bias4(const float* b, int lane) {
   return *reinterpret_cast<const f32x4*>(b + 4 * (lane >> 4));
-}
-
-// Forward pass of one wavefront: 64 samples, sample s = 16 n + (l % 16) in tile column n.
-// xs: [64][16] bfloat16 inputs (row = sample). On return z1, z2 hold the pre-activations and
-// h1, h2 the bfloat16 activations in the C layout, y the outputs (C layout, rows 0..8 valid).
-struct MlpAct {
-  f32x4 z1[4][4], z2[4][4];  // [m][n]
-  bf16x4 h1[4][4], h2[4][4];
-  f32x4 y[4];                // [n]
-};
-
-__device__ __forceinline__ void mlp_forward_wave(const MlpLds& s, const short (*xs)[16],
-                                                 MlpAct& a, bool keep_z) {
-  const int lane = threadIdx.x & 63;
-  const int r = lane & 15, q = lane >> 4;
-  // layer 1: K = 16 (12 inputs + zero padding)
-#pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    const bf16x4 xb = ld4(&xs[16 * n + r][4 * q]);
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      f32x4 acc = bias4(s.b1 + 16 * m, lane);
-      acc = mfma16(ld4(&s.w1[16 * m + r][4 * q]), xb, acc);
-      if (keep_z) a.z1[m][n] = acc;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) a.h1[m][n][j] = f2bf(gelu(acc[j]));
-    }
-  }
-  // layer 2: K = 64
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    bf16x4 wa[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) wa[k] = ld4(&s.w2[16 * m + r][16 * k + 4 * q]);
-#pragma unroll
-    for (int n = 0; n < 4; ++n) {
-      f32x4 acc = bias4(s.b2 + 16 * m, lane);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) acc = mfma16(wa[k], a.h1[k][n], acc);
-      if (keep_z) a.z2[m][n] = acc;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) a.h2[m][n][j] = f2bf(gelu(acc[j]));
-    }
-  }
-  // layer 3: 9 outputs padded to 16
-  bf16x4 w3a[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) w3a[k] = ld4(&s.w3[r][16 * k + 4 * q]);
-#pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    f32x4 acc = bias4(s.b3, lane);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) acc = mfma16(w3a[k], a.h2[k][n], acc);
-    a.y[n] = acc;
-  }
-}
-
-// Forward pass of node tile n (16 samples) only: the activations of one tile stay in
-// registers (8 VGPRs per layer), which keeps the inference kernel's register count low.
-// Returns the output tile (C layout, rows 0..8 valid).
-__device__ __forceinline__ f32x4 mlp_forward_tile(const MlpLds& s, const short (*xs)[16], int n) {
-  const int lane = threadIdx.x & 63;
-  const int r = lane & 15, q = lane >> 4;
-  const bf16x4 xb = ld4(&xs[16 * n + r][4 * q]);
-  bf16x4 h1[4], h2[4];
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    f32x4 acc = bias4(s.b1 + 16 * m, lane);
-    acc = mfma16(ld4(&s.w1[16 * m + r][4 * q]), xb, acc);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) h1[m][j] = f2bf(gelu(acc[j]));
-  }
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    f32x4 acc = bias4(s.b2 + 16 * m, lane);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) acc = mfma16(ld4(&s.w2[16 * m + r][16 * k + 4 * q]), h1[k], acc);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) h2[m][j] = f2bf(gelu(acc[j]));
-  }
-  f32x4 acc = bias4(s.b3, lane);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) acc = mfma16(ld4(&s.w3[r][16 * k + 4 * q]), h2[k], acc);
-  return acc;
 }
 
 // Inference tile (16 samples, tile column n) on the CDNA4 double-K matrix tiles: layer 1 is one
@@ -303,6 +204,40 @@ __device__ __forceinline__ void project9(float (&y)[9]) {
   for (int i = 0; i < 9; ++i)
     y[i] -= s * (1.0f / 9.0f) + (float)(i % 3 - 1) * sx * (1.0f / 6.0f) +
             (float)(i / 3 - 1) * sy * (1.0f / 6.0f);
+}
+
+// Training: project9 of the outputs, and project9 of scale d (the output gradient).
+__device__ __forceinline__ void project9_outputs(float (&y)[9]) {
+#pragma clang fp contract(off)
+  float s = 0.0f, sx = 0.0f, sy = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    s += y[i];
+    if (i % 3 != 1) sx += i % 3 ? y[i] : -y[i];
+    if (i / 3 != 1) sy += i / 3 ? y[i] : -y[i];
+  }
+  const float m = s * (1.0f / 9.0f), px = sx * (1.0f / 6.0f), py = sy * (1.0f / 6.0f);
+  const float col[3] = {__builtin_fmaf(s, 1.0f / 9.0f, -px), m, m + px};
+  const float row[3] = {-py, 0.0f, py};
+#pragma unroll
+  for (int i = 0; i < 9; ++i) y[i] -= row[i / 3] + col[i % 3];
+}
+__device__ __forceinline__ void project9_gradient(const float (&d)[9], float scale, float (&dy)[9]) {
+#pragma clang fp contract(off)
+  float s = 0.0f, sx = 0.0f, sy = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    s = __builtin_fmaf(scale, d[i], s);
+    if (i % 3 != 1) sx = __builtin_fmaf(i % 3 ? scale : -scale, d[i], sx);
+    if (i / 3 != 1) sy = __builtin_fmaf(i / 3 ? scale : -scale, d[i], sy);
+  }
+  const float w = 1.0f / 6.0f, m = s * (1.0f / 9.0f);
+  const float col[3] = {__builtin_fmaf(sx, -w, m), m, __builtin_fmaf(sx, w, m)};
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    const float p = i / 3 == 1 ? col[i % 3] : __builtin_fmaf(sy, i / 3 ? w : -w, col[i % 3]);
+    dy[i] = __builtin_fmaf(scale, d[i], -p);
+  }
 }
 
 // Network inputs of one node from pre-collision f and its moments (theta = 1/3 equilibrium).
