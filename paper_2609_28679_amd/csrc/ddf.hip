@@ -42,6 +42,7 @@
 #include "ddf_common.h"
 #include "reduced_common.h"
 
+#include <algorithm>
 #include <cstdlib>
 #include <type_traits>
 
@@ -635,15 +636,49 @@ k_ddf_neq_rows(const S* __restrict__ A, int nx, int ny, int64_t pitch, int64_t p
 // steps keep their 4 (552 / 568 at 6 and 561 / 580).
 constexpr int kDdfExtRows = 8;
 
+// Lattices that do not fill the chip several times over get lower windows: the rows in
+// [1, G.rows] that take the least window rows in turn, rounds of resident workgroups x (rows + 2
+// halo + 1 for the start). Three workgroups fit a compute unit for the plain float32 step with
+// central Phi, two otherwise. us per step, the fixed rows -> these: 64^2 plain 9.6 -> 5.9, upwind
+// 28.1 -> 7.9, float16 44.6 -> 11.5, Pr 0.71 with NEQ walls 21.9 -> 10.5; 512^2 plain 16.0 ->
+// 13.8, upwind 38.5 -> 22; 1021 x 509 Pr 0.71 with NEQ walls 38.3 -> 30.6, float16 48.7 -> 32.
+static Grid ddf_fill(Grid G, const Layout& L, int halo, int per_cu) {
+  const int64_t slots = 256 * per_cu;
+  int64_t best = -1;
+  int rows = G.rows;
+  for (int r = 1; r <= G.rows; ++r) {
+    const int64_t blocks = (int64_t)G.nbx * ((L.ny + r - 1) / r);
+    const int64_t cost = (blocks + slots - 1) / slots * (r + 2 * halo + 1);
+    if (best < 0 || cost <= best) {
+      best = cost;
+      rows = r;
+    }
+  }
+  G.rows = rows;
+  fit_rows(G, L.ny);
+  return G;
+}
+
+// Launch grid of one step, from the plan's grid: taller windows for the extended collisions.
+static Grid ddf_step_grid(Grid G, const Layout& L, int phi, int fmt, bool extended) {
+  if (fmt < 2 && extended && G.rows < kDdfExtRows) {
+    G.rows = kDdfExtRows;
+    fit_rows(G, L.ny);
+  }
+  const int halo = phi == 2 ? 2 : 1;
+  return ddf_fill(G, L, halo, fmt == 0 && halo == 1 && !extended ? 3 : 2);
+}
+
+int ddf_max_records(const Layout& L, const Grid& G, int phi, int fmt) {
+  return std::max(ddf_step_grid(G, L, phi, fmt, false).blocks(),
+                  ddf_step_grid(G, L, phi, fmt, true).blocks());
+}
+
 hipError_t launch_ddf(int fmt, bool walls, bool pull, const void* A, void* B, const Layout& L,
                       const Grid& G0, const DdfParams& prm, float s_enc, float s_dec,
                       double* partials, void* nb, int* records, hipStream_t s) {
   if (prm.ext() && fmt >= 2) return hipErrorInvalidValue;  // no extended path with reduced storage
-  Grid G = G0;
-  if (fmt < 2 && (prm.ext() || prm.eos) && G.rows < kDdfExtRows) {
-    G.rows = kDdfExtRows;
-    fit_rows(G, L.ny);
-  }
+  const Grid G = ddf_step_grid(G0, L, prm.phi, fmt, prm.ext() || prm.eos);
   if (records) *records = G.blocks();
   if (prm.neq) {
     if (fmt >= 2 || !walls || !nb || L.ny < 3 || prm.src) return hipErrorInvalidValue;

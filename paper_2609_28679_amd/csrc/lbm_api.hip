@@ -255,6 +255,9 @@ void make_plan(const lbm_params* p, Plan& P) {
   else
     P.G = make_grid(P.L);
   P.partial_slots = std::max(P.G.blocks(), 1024);
+  if (P.ddf && P.D == 2)  // small lattices and extended collisions have their own windows
+    P.partial_slots = std::max(P.partial_slots,
+                               ddf_max_records(P.L, P.G, p->phi, P.codec >= 0 ? 2 + P.codec : P.kind));
   if (P.ddf && P.D == 3)  // the one-launch step and the upwind sweeps have their own grids
     P.partial_slots = (int)std::max<int64_t>(P.partial_slots, ddf3_max_records(P.L, P.G));
   // One in-place buffer where supported and either requested or small enough to profit from
