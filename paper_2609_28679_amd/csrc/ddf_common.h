@@ -18,13 +18,25 @@ struct Axis {
   double chi[3];
 };
 
+// a b + c d with the product a b fused to the sum
+__device__ __forceinline__ double product_last(double a, double b, double c, double d) {
+#pragma clang fp contract(off)
+  return __builtin_fma(a, b, c * d);
+}
+
+// FUSED: which product of a1 is fused to the sum (1 theta v, 2 v^3/2; 0 the compiler's choice). It
+// is written out in the two-step kernel (k_ddf_pair), where the compiler chooses otherwise than in
+// the one-step kernel, so that both round alike.
+template <int FUSED = 0>
 __device__ __forceinline__ void axis_eq(double v, double theta, Axis& a) {
   const double v2 = v * v;
   a.psi[1] = 1.0 - theta - v2;
   a.psi[2] = 0.5 * (theta + v2 + v);
   a.psi[0] = 0.5 * (theta + v2 - v);
   const double a0 = 0.5 * v2;
-  const double a1 = theta * v + 0.5 * v2 * v;
+  const double a1 = FUSED == 1   ? product_last(theta, v, 0.5 * v2, v)
+                    : FUSED == 2 ? product_last(0.5 * v2, v, theta, v)
+                                 : theta * v + 0.5 * v2 * v;
   const double a2 = theta * theta + 2.5 * theta * v2 + 0.5 * v2 * v2;
   a.chi[1] = a0 - a2;
   a.chi[2] = 0.5 * (a2 + a1);
@@ -220,7 +232,7 @@ __device__ __forceinline__ double upwind_or_central(double pm2, double pm1, doub
 // m[6], m[7], dTdy, duydy are used only when p.full; for the van der Waals fluid (VDW)
 // gamma - 1 and alpha are per node and q^c = P (grad h - (k/mu) grad T) with h = e + P/rho
 // (m[8], dhdy).
-template <bool EXT = false, bool VDW = false, typename R, typename Sink>
+template <bool EXT = false, bool VDW = false, bool FUSED = false, typename R, typename Sink>
 __device__ __forceinline__ void collide_ddf(const R (&hf)[9], const R (&hg)[9],
                                             const double* m, double phxx, double phyy,
                                             double dTdy, double duydy, double dhdy,
@@ -228,8 +240,8 @@ __device__ __forceinline__ void collide_ddf(const R (&hf)[9], const R (&hg)[9],
   const double rho = m[0], theta = m[3], e = m[4];
   const double P = rho * theta;
   Axis X, Y;
-  axis_eq(m[1], theta, X);
-  axis_eq(m[2], theta, Y);
+  axis_eq<FUSED ? 1 : 0>(m[1], theta, X);
+  axis_eq<FUSED ? 1 : 0>(m[2], theta, Y);
   // shifted state: the factors of f*, g* (the unshifted ones without the extended path)
   Axis XS = X, YS = Y;
   double es = e, qx = 0.0, qy = 0.0;
@@ -253,8 +265,8 @@ __device__ __forceinline__ void collide_ddf(const R (&hf)[9], const R (&hg)[9],
         qy = P * p.qc * dTdy;
       }
     }
-    axis_eq(m[1] + p.Fx * inv, thetas, XS);
-    axis_eq(m[2] + p.Fy * inv, thetas, YS);
+    axis_eq<FUSED ? 2 : 0>(m[1] + p.Fx * inv, thetas, XS);
+    axis_eq<FUSED ? 2 : 0>(m[2] + p.Fy * inv, thetas, YS);
     es = e + p.Q * inv - 0.5 * (p.Fx * p.Fx + p.Fy * p.Fy) * inv * inv;
   }
   // Psi(c; u*, theta* + u*^2 + Phi): psi* + Phi * (1/2, -1, 1/2)
@@ -274,9 +286,13 @@ __device__ __forceinline__ void collide_ddf(const R (&hf)[9], const R (&hg)[9],
     const double hfe = rho * pp - p.wf[i];  // f^eq - w
     const double f = (double)hf[i];
     const double g = (double)hg[i];
+    // FUSED: the choices the compiler makes in the one-step kernel
+    const double gq = !FUSED ? e * pp + X.chi[a] * Y.psi[b]
+                             : (a == 1 && b != 1 ? product_last(X.chi[a], Y.psi[b], e, pp)
+                                                 : product_last(e, pp, X.chi[a], Y.psi[b]));
     if (EXT) {
       const double fe = rho * pp;
-      const double ge = rho * (e * pp + X.chi[a] * Y.psi[b] + X.psi[a] * Y.chi[b]);
+      const double ge = rho * (gq + X.psi[a] * Y.chi[b]);
       double gs = rho * (es * (XS.psi[a] * YS.psi[b]) + XS.chi[a] * YS.psi[b] +
                          XS.psi[a] * YS.chi[b]);
       if (i == 1) gs -= 0.5 * qy;  // c = (0, -1)
@@ -287,7 +303,7 @@ __device__ __forceinline__ void collide_ddf(const R (&hf)[9], const R (&hg)[9],
       sink(i, f + omega * (hfe - f) + keep * (rho * (sx[a] * sy[b]) - fe), hfe,
            g + omega * (hge - g) + keep * (gs - ge), hge);
     } else {
-      const double hge = rho * (e * pp + X.chi[a] * Y.psi[b] + X.psi[a] * Y.chi[b]) - p.wg[i];
+      const double hge = rho * (gq + X.psi[a] * Y.chi[b]) - p.wg[i];
       const double dstar = rho * (sx[a] * sy[b] - pp);  // f* - f^eq
       sink(i, f + omega * (hfe - f) + keep * dstar, hfe, g + omega * (hge - g), hge);
     }

@@ -139,6 +139,11 @@ hipError_t launch_ddf(int fmt, bool walls, bool pull, const void* A, void* B, co
                       double* partials, void* nb, int* records, hipStream_t s);
 // Most diagnostics records any step of the format writes (grid G of the plan).
 int ddf_max_records(const Layout& L, const Grid& G, int phi, int fmt);
+// Two steps in one launch, from A to B (float32 / float64 storage, phi 0 or 1); NEQ walls rebuild
+// their rows inside.
+bool ddf_pair_supported(int fmt, const Layout& L, const DdfParams& prm);
+hipError_t launch_ddf_pair(int fmt, bool walls, const void* A, void* B, const Layout& L,
+                           const DdfParams& prm, hipStream_t s);
 hipError_t launch_init_ddf(int kind, const double* rho, const double* u, const double* T,
                            void* A, const Layout& L, const DdfParams& prm, hipStream_t s);
 hipError_t launch_moments_ddf(int kind, const void* A, const Layout& L, const DdfParams& prm,
