@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbm.so")
 
-SOURCES = ["lbm_api.hip", "host_copy.hip", "bgk.hip", "bgk_multi.hip", "ddf.hip", "ddf_pair.hip", "ddf3.hip", "reduced.hip", "mlp.hip", "copy.hip"]
+SOURCES = ["lbm_api.hip", "host_copy.hip", "bgk.hip", "bgk_multi.hip", "bgk3_multi.hip", "ddf.hip", "ddf_pair.hip", "ddf3.hip", "reduced.hip", "mlp.hip", "copy.hip"]
 
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

@@ -31,6 +31,7 @@ struct lbm_ctx {
   int codec = -1;    // reduced storage: 0 = bfloat16, 1 = float16 (scaled); -1 = none
   float s_enc = 1.0f, s_dec = 1.0f;
   int planes = 9;    // stored population planes per buffer
+  bool pair3 = false;  // isothermal D3Q27: two steps per launch (while no force is set)
   bool multi = false;  // several steps per launch, from one buffer into the other
   bool aa = false;   // one buffer, in place (isothermal model): layout alternates with t parity
   DdfParams dp{};
@@ -480,6 +481,7 @@ int lbm_create(const lbm_params* p, const double* rho0, const double* u0, const 
   c->ws_bytes = P.total;
   c->A = c->ws + P.off_A;
   c->multi = P.multi;
+  c->pair3 = !P.ddf && P.D == 3 && !P.aa && P.kind == 0 && !p->wall_y && p->nx <= 1 << 24;
   c->B = P.aa ? (P.multi ? c->ws + P.off_read : nullptr) : c->ws + P.off_B;
   c->partials = reinterpret_cast<double*>(c->ws + P.off_part);
   c->history = reinterpret_cast<double*>(c->ws + P.off_hist);
@@ -559,6 +561,14 @@ int lbm_step(lbm_ctx* c, int64_t n) {
         c->F_state = c->F;
       }
       if (k >= n) break;
+    }
+    if (c->pair3 && !c->F.on() && n - k >= 2 && (de == 0 || c->t % de < de - 2)) {
+      HIP_TRY(c, launch_bgk_d3q27_pair(c->A, c->B, c->L, c->omega, c->stream));
+      std::swap(c->A, c->B);
+      c->t += 2;
+      ++k;
+      c->F_state = c->F;
+      continue;
     }
     if (c->ddf && c->D == 2 && n - k >= 2 && ddf_pair_supported(c->fmt, c->L, c->dp) &&
         (de == 0 || c->t % de < de - 2)) {

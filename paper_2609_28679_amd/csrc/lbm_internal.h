@@ -112,6 +112,9 @@ constexpr int kMultiSteps = 6;
 hipError_t launch_bgk_d2q9_multi(int kind, const void* A, void* B, const Layout& L, bool swapped,
                                  double omega, const Force& F, bool walls, int steps,
                                  hipStream_t s);
+// Two D3Q27 steps in one launch, from A to B (two buffers, float32, periodic, no force).
+hipError_t launch_bgk_d3q27_pair(const void* A, void* B, const Layout& L, double omega,
+                                 hipStream_t s);
 // swap: store population i in slot Q-1-i (single-buffer state at an even step count). With a
 // force the equilibrium is collided once (the stored state is post-collision at t = 0).
 hipError_t launch_init_bgk(int kind, int D, const double* rho, const double* u, void* A,

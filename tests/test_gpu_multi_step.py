@@ -54,3 +54,29 @@ def test_multi_step_two_buffers():
             assert np.array_equal(many.populations()[0], single.populations()[0])
         many.close()
         single.close()
+
+
+# rows around the 9 owned ones of a tile and below its halo, columns around 64, few and odd planes
+@pytest.mark.parametrize("nx,ny,nz", [(1, 1, 1), (2, 3, 1), (63, 9, 5), (64, 10, 12), (65, 19, 3),
+                                      (130, 28, 7), (37, 20, 130)])
+def test_d3q27_two_steps_equal_single_steps(nx, ny, nz):
+    from paper_2609_28679_amd import binding
+    rng = np.random.default_rng(3)
+    rho = 1.0 + 0.01 * rng.standard_normal((nz, ny, nx))
+    u = 0.03 * rng.standard_normal((3, nz, ny, nx))
+    kw = dict(lattice="D3Q27", tau=0.6, streaming="two", diag_every=7)
+    many, single = binding.Lattice(rho, u, **kw), binding.Lattice(rho, u, **kw)
+    for n in (4, 9):  # pairs, then pairs and single steps around the entry at t = 7
+        many.step(n)
+        for _ in range(n):
+            single.step(1)
+        assert np.array_equal(many.populations()[0], single.populations()[0]), n
+    assert np.array_equal(many.diag_history(), single.diag_history())
+    many.set_force((1e-5, 0.0, 0.0))  # one step per launch from here on
+    single.set_force((1e-5, 0.0, 0.0))
+    many.step(2)
+    for _ in range(2):
+        single.step(1)
+    assert np.array_equal(many.populations()[0], single.populations()[0])
+    many.close()
+    single.close()
