@@ -26,11 +26,16 @@ struct HostPiece {
 // 256 MiB 6 x 4 MiB (403 MB: 10.5 ms; 4 x 2: 11.4, 3 x 4: 12.2, 1 x 4: 29), above 16 MiB 4 x
 // 2 MiB (101 MB: 3.2 ms, the first call 5.7; 6 x 4: 3.1, the first call 7.6, most of it the pinned
 // allocation), above 4 MiB 4 x 1 MiB; below, the plain copy, whose time the threads would not
-// repay. The staging memory belongs to the object, which copies for one caller at a time like
-// the context that owns it.
+// repay. An object copies for one caller at a time like the context that owns it; several objects
+// may copy at once. The staging memory is shared by the objects of the process, one slab per copy
+// under way.
 class HostCopy {
  public:
-  HostCopy() = default;
+  struct Slab {
+    char* p = nullptr;
+    size_t bytes = 0;
+  };
+  HostCopy();
   HostCopy(const HostCopy&) = delete;
   HostCopy& operator=(const HostCopy&) = delete;
   ~HostCopy();
@@ -42,12 +47,11 @@ class HostCopy {
     int threads;
     size_t chunk;
   };
-  bool reserve(const Shape& sh);
-  void release();
-  hipError_t lane(int w, const Shape& sh, const HostPiece* p, int n, size_t total, int device,
-                  hipStream_t s);
-  char* slab_ = nullptr;  // two chunks per thread
-  size_t slab_bytes_ = 0;
+  static bool take(size_t bytes, Slab& slab);
+  static void give(const Slab& slab);
+  bool events(int n);
+  hipError_t lane(int w, const Shape& sh, char* slab, const HostPiece* p, int n, size_t total,
+                  int device, hipStream_t s);
   std::vector<hipEvent_t> ev_;  // two per thread
 };
 
