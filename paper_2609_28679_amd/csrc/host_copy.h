@@ -1,4 +1,4 @@
-// Device-to-host copies of read-outs.
+// Copies of read-outs and initial fields between device and host.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -10,13 +10,13 @@
 namespace lbm {
 
 struct HostPiece {
-  void* dst;        // host memory of the caller (pageable)
-  const void* src;  // device memory
+  void* dst;        // one of them device memory, the other the caller's pageable host memory
+  const void* src;
   size_t bytes;
 };
 
-// Copies from the device through pinned staging buffers, several host threads moving them on to
-// the caller's memory. A plain copy to pageable memory runs through one staging path of the
+// Copies through pinned staging buffers, several host threads moving them on to the caller's memory
+// (or from it, for the initial fields: a 2048^2 context took 37-43 ms to make, most of it uploads). A plain copy to pageable memory runs through one staging path of the
 // runtime on one host thread, which also takes the page faults of newly allocated memory: about
 // 10 GB/s, 20-30% of an output interval. Measured for a whole read-out (moments kernel, totals
 // and copy): 4096^2 D2Q9, 403 MB, 40 -> 10.5 ms; 2048^2, 101 MB, 10 -> 3.2 ms.
@@ -39,8 +39,8 @@ class HostCopy {
   HostCopy(const HostCopy&) = delete;
   HostCopy& operator=(const HostCopy&) = delete;
   ~HostCopy();
-  // Copies the pieces after the work queued on s; returns when they are in host memory.
-  hipError_t copy(const HostPiece* p, int n, int device, hipStream_t s);
+  // Copies the pieces after the work queued on s, from the device or to it; returns when done.
+  hipError_t copy(const HostPiece* p, int n, hipMemcpyKind kind, int device, hipStream_t s);
 
  private:
   struct Shape {
@@ -51,7 +51,7 @@ class HostCopy {
   static void give(const Slab& slab);
   bool events(int n);
   hipError_t lane(int w, const Shape& sh, char* slab, const HostPiece* p, int n, size_t total,
-                  int device, hipStream_t s);
+                  hipMemcpyKind kind, int device, hipStream_t s);
   std::vector<hipEvent_t> ev_;  // two per thread
 };
 

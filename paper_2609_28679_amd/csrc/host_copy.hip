@@ -78,7 +78,7 @@ bool HostCopy::events(int n) {
 
 // Chunks w, w + threads, ... of the concatenated pieces.
 hipError_t HostCopy::lane(int w, const Shape& sh, char* slab, const HostPiece* p, int n,
-                          size_t total, int device, hipStream_t s) {
+                          size_t total, hipMemcpyKind kind, int device, hipStream_t s) {
   hipError_t e = hipSetDevice(device);  // a thread's current device is its own
   // fn(piece, offset in it, length, offset in the chunk) for the parts of chunk c
   auto parts = [&](size_t c, auto&& fn) {
@@ -100,6 +100,19 @@ hipError_t HostCopy::lane(int w, const Shape& sh, char* slab, const HostPiece* p
   };
   const size_t chunks = (total + sh.chunk - 1) / sh.chunk;
   int k = 0;
+  if (kind == hipMemcpyHostToDevice) {
+    for (size_t c = w; c < chunks && e == hipSuccess; c += sh.threads, k ^= 1) {
+      if (c >= (size_t)w + 2 * sh.threads) e = hipEventSynchronize(ev_[2 * w + k]);
+      if (e != hipSuccess) break;
+      parts(c, [&](const HostPiece& q, size_t off, size_t len, size_t at) {
+        std::memcpy(buf(k) + at, static_cast<const char*>(q.src) + off, len);
+        if (e == hipSuccess)
+          e = hipMemcpyAsync(static_cast<char*>(q.dst) + off, buf(k) + at, len, kind, s);
+      });
+      if (e == hipSuccess) e = hipEventRecord(ev_[2 * w + k], s);
+    }
+    return e;
+  }
   if ((size_t)w < chunks && e == hipSuccess) fetch(w, 0);
   for (size_t c = w; c < chunks && e == hipSuccess; c += sh.threads, k ^= 1) {
     if (c + sh.threads < chunks) fetch(c + sh.threads, k ^ 1);
@@ -112,7 +125,8 @@ hipError_t HostCopy::lane(int w, const Shape& sh, char* slab, const HostPiece* p
   return e;
 }
 
-hipError_t HostCopy::copy(const HostPiece* p, int n, int device, hipStream_t s) {
+hipError_t HostCopy::copy(const HostPiece* p, int n, hipMemcpyKind kind, int device,
+                          hipStream_t s) {
   size_t total = 0;
   for (int i = 0; i < n; ++i) total += p[i].bytes;
   const size_t mib = (size_t)1 << 20;
@@ -122,7 +136,7 @@ hipError_t HostCopy::copy(const HostPiece* p, int n, int device, hipStream_t s) 
   if (total <= 4 * mib || !events(2 * sh.threads) || !take(2 * sh.threads * sh.chunk, slab)) {
     hipError_t e = hipSuccess;
     for (int i = 0; i < n && e == hipSuccess; ++i)
-      e = hipMemcpyAsync(p[i].dst, p[i].src, p[i].bytes, hipMemcpyDeviceToHost, s);
+      e = hipMemcpyAsync(p[i].dst, p[i].src, p[i].bytes, kind, s);
     const hipError_t es = hipStreamSynchronize(s);
     return e != hipSuccess ? e : es;
   }
@@ -131,11 +145,11 @@ hipError_t HostCopy::copy(const HostPiece* p, int n, int device, hipStream_t s) 
   int started = 1;  // this thread takes lane 0, and the lanes that get no thread
   try {
     for (; started < sh.threads; ++started)
-      th[started] = std::thread([&, w = started] { res[w] = lane(w, sh, slab.p, p, n, total, device, s); });
+      th[started] = std::thread([&, w = started] { res[w] = lane(w, sh, slab.p, p, n, total, kind, device, s); });
   } catch (...) {
   }
-  res[0] = lane(0, sh, slab.p, p, n, total, device, s);
-  for (int w = started; w < sh.threads; ++w) res[w] = lane(w, sh, slab.p, p, n, total, device, s);
+  res[0] = lane(0, sh, slab.p, p, n, total, kind, device, s);
+  for (int w = started; w < sh.threads; ++w) res[w] = lane(w, sh, slab.p, p, n, total, kind, device, s);
   for (int w = 1; w < started; ++w) th[w].join();
   // also after an error: nothing still writes to the staging memory when it is given back
   hipError_t e = hipStreamSynchronize(s);

@@ -497,15 +497,14 @@ int lbm_create(const lbm_params* p, const double* rho0, const double* u0, const 
   }
   // padding between rows and planes is never read by the kernels, but keep it defined
   hipError_t e = hipMemsetAsync(c->ws, 0, P.off_read, c->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(c->readout, rho0, nodes * sizeof(double), hipMemcpyHostToDevice, c->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(c->readout + nodes, u0, (size_t)P.D * nodes * sizeof(double), hipMemcpyHostToDevice, c->stream);
+  // the fields go to the read-out area in one piece each: rho, u, T
+  double* const d_T0 = c->readout + (size_t)(1 + P.D) * nodes;
+  const size_t field = (size_t)nodes * sizeof(double);
+  const HostPiece init[3] = {{c->readout, rho0, field}, {c->readout + nodes, u0, P.D * field}, {d_T0, T0, field}};
+  if (e == hipSuccess) e = c->host_copy.copy(init, P.ddf ? 3 : 2, hipMemcpyHostToDevice, c->device, c->stream);
   if (P.ddf) {
     // Fig. 1: f <- f^eq, g <- g^eq into B, then one collide-only pass B -> A so that A holds
     // the post-collision state of t = 0 (f* differs from f^eq when Phi is on)
-    double* d_T0 = c->readout + (size_t)(1 + P.D) * nodes;
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(d_T0, T0, nodes * sizeof(double), hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess)
       e = P.D == 2 ? launch_ddf_rest_state(c->dp, c->partials, c->stream)
                    : launch_ddf3_rest_state(c->dp, c->partials, c->stream);
@@ -701,7 +700,7 @@ int lbm_moments(lbm_ctx* c, double* rho, double* u, double* T, double* totals) {
   if (rho) out[pieces++] = {rho, d_rho, field};
   if (u) out[pieces++] = {u, d_u, c->D * field};
   if (T && c->ddf) out[pieces++] = {T, d_T, field};
-  HIP_TRY(c, c->host_copy.copy(out, pieces, c->device, c->stream));
+  HIP_TRY(c, c->host_copy.copy(out, pieces, hipMemcpyDeviceToHost, c->device, c->stream));
   return LBM_OK;
 }
 
@@ -719,7 +718,7 @@ int lbm_populations(lbm_ctx* c, double* f, double* g) {
     else
       HIP_TRY(c, launch_decode_f(c->kind, c->D, i, c->A, c->L, view_of(c), c->p.wall_y != 0, c->readout, c->stream));
     const HostPiece out{dst, c->readout, nodes * sizeof(double)};
-    HIP_TRY(c, c->host_copy.copy(&out, 1, c->device, c->stream));
+    HIP_TRY(c, c->host_copy.copy(&out, 1, hipMemcpyDeviceToHost, c->device, c->stream));
   }
   return LBM_OK;
 }
