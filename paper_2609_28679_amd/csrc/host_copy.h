@@ -5,9 +5,10 @@
 
 #include <cstddef>
 #include <cstdint>
-#include <vector>
 
 namespace lbm {
+
+constexpr int kMaxBuffers = 12;  // staging buffers of one copy
 
 struct HostPiece {
   void* dst;        // one of them device memory, the other the caller's pageable host memory
@@ -16,19 +17,18 @@ struct HostPiece {
 };
 
 // Copies through pinned staging buffers, several host threads moving them on to the caller's memory
-// (or from it, for the initial fields: a 2048^2 context took 37-43 ms to make, most of it uploads). A plain copy to pageable memory runs through one staging path of the
+// (or from it, for the initial fields). A plain copy to pageable memory runs through one staging path of the
 // runtime on one host thread, which also takes the page faults of newly allocated memory: about
 // 10 GB/s, 20-30% of an output interval. Measured for a whole read-out (moments kernel, totals
 // and copy): 4096^2 D2Q9, 403 MB, 40 -> 10.5 ms; 2048^2, 101 MB, 10 -> 3.2 ms.
 //
-// Each thread alternates between two buffers, the next chunk in flight while it moves the last.
-// Threads x chunk by the bytes of the call, from sweeps of 1-16 threads and 1-8 MiB: above
-// 256 MiB 6 x 4 MiB (403 MB: 10.5 ms; 4 x 2: 11.4, 3 x 4: 12.2, 1 x 4: 29), above 16 MiB 4 x
-// 2 MiB (101 MB: 3.2 ms, the first call 5.7; 6 x 4: 3.1, the first call 7.6, most of it the pinned
-// allocation), above 4 MiB 4 x 1 MiB; below, the plain copy, whose time the threads would not
-// repay. An object copies for one caller at a time like the context that owns it; several objects
-// may copy at once. The staging memory is shared by the objects of the process, one slab per copy
-// under way.
+// Threads x chunk by the bytes of the call, two chunks in flight per thread, from sweeps of 1-16
+// threads and 1-8 MiB: above 256 MiB 6 x 4 MiB (403 MB: 10.5 ms; 4 x 2: 11.4, 3 x 4: 12.2, 1 x 4:
+// 29), above 16 MiB 4 x 2 MiB (101 MB: 3.2 ms, the first call 5.7; 6 x 4: 3.1, the first call 7.6,
+// most of it the pinned allocation), above 4 MiB 4 x 1 MiB; below, the plain copy, whose time the
+// threads would not repay. An object copies for one caller at a time like the context that owns it;
+// several objects may copy at once. The staging memory is shared by the objects of the process, one
+// slab per copy under way.
 class HostCopy {
  public:
   struct Slab {
@@ -40,19 +40,14 @@ class HostCopy {
   HostCopy& operator=(const HostCopy&) = delete;
   ~HostCopy();
   // Copies the pieces after the work queued on s, from the device or to it; returns when done.
-  hipError_t copy(const HostPiece* p, int n, hipMemcpyKind kind, int device, hipStream_t s);
+  hipError_t copy(const HostPiece* p, int n, hipMemcpyKind kind, hipStream_t s);
 
  private:
-  struct Shape {
-    int threads;
-    size_t chunk;
-  };
   static bool take(size_t bytes, Slab& slab);
   static void give(const Slab& slab);
   bool events(int n);
-  hipError_t lane(int w, const Shape& sh, char* slab, const HostPiece* p, int n, size_t total,
-                  hipMemcpyKind kind, int device, hipStream_t s);
-  std::vector<hipEvent_t> ev_;  // two per thread
+  hipEvent_t ev_[kMaxBuffers];  // one per staging buffer
+  int events_ = 0;
 };
 
 }  // namespace lbm

@@ -1,6 +1,7 @@
 #include "host_copy.h"
 
 #include <algorithm>
+#include <condition_variable>
 #include <cstring>
 #include <mutex>
 #include <thread>
@@ -12,8 +13,8 @@ namespace lbm {
 namespace {
 std::mutex g_mutex;
 int g_objects = 0;
-std::vector<HostCopy::Slab> g_idle;
-constexpr size_t kMaxIdle = 2;
+constexpr int kMaxIdle = 2;
+HostCopy::Slab g_idle[kMaxIdle];
 }  // namespace
 
 HostCopy::HostCopy() {
@@ -22,22 +23,24 @@ HostCopy::HostCopy() {
 }
 
 HostCopy::~HostCopy() {
-  for (hipEvent_t e : ev_) (void)hipEventDestroy(e);
-  std::vector<Slab> drop;
+  for (int i = 0; i < events_; ++i) (void)hipEventDestroy(ev_[i]);
+  Slab drop[kMaxIdle];
   {
     std::lock_guard<std::mutex> lock(g_mutex);
-    if (--g_objects == 0) drop.swap(g_idle);
+    if (--g_objects == 0)
+      for (int i = 0; i < kMaxIdle; ++i) std::swap(drop[i], g_idle[i]);
   }
-  for (const Slab& s : drop) (void)hipHostFree(s.p);
+  for (const Slab& d : drop)
+    if (d.p) (void)hipHostFree(d.p);
 }
 
 bool HostCopy::take(size_t bytes, Slab& slab) {
   {
     std::lock_guard<std::mutex> lock(g_mutex);
-    for (size_t i = 0; i < g_idle.size(); ++i)
-      if (g_idle[i].bytes >= bytes) {
-        slab = g_idle[i];
-        g_idle.erase(g_idle.begin() + i);
+    for (Slab& idle : g_idle)
+      if (idle.bytes >= bytes) {
+        slab = idle;
+        idle = Slab{};
         return true;
       }
   }
@@ -54,109 +57,144 @@ void HostCopy::give(const Slab& slab) {
   Slab drop = slab;
   {
     std::lock_guard<std::mutex> lock(g_mutex);
-    if (g_idle.size() < kMaxIdle) {
-      g_idle.push_back(slab);
-      return;
-    }
-    for (Slab& s : g_idle)
-      if (s.bytes < drop.bytes) std::swap(s, drop);  // the largest stay
+    for (Slab& idle : g_idle)
+      if (idle.bytes < drop.bytes) std::swap(idle, drop);  // the largest stay
   }
-  (void)hipHostFree(drop.p);
+  if (drop.p) (void)hipHostFree(drop.p);
 }
 
 bool HostCopy::events(int n) {
-  while ((int)ev_.size() < n) {
-    hipEvent_t e;
-    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+  for (; events_ < n; ++events_)
+    if (hipEventCreateWithFlags(&ev_[events_], hipEventDisableTiming) != hipSuccess) {
       (void)hipGetLastError();
       return false;
     }
-    ev_.push_back(e);
-  }
   return true;
 }
 
-// Chunks w, w + threads, ... of the concatenated pieces.
-hipError_t HostCopy::lane(int w, const Shape& sh, char* slab, const HostPiece* p, int n,
-                          size_t total, hipMemcpyKind kind, int device, hipStream_t s) {
-  hipError_t e = hipSetDevice(device);  // a thread's current device is its own
+namespace {
+// One staged copy under way. The calling thread alone works on the stream, whose handle may mean
+// another queue in another thread (hipStreamPerThread): it queues the copies of the chunks between
+// device and buffers in order, chunk c in buffer c mod `buffers`, with an event behind each. The
+// movers take the chunks in order and move them between the buffers and the caller's memory.
+struct Staging {
+  const HostPiece* p;
+  int n;
+  hipMemcpyKind kind;
+  hipStream_t s;
+  char* slab;
+  hipEvent_t* ev;
+  size_t chunk, total, chunks;
+  int buffers;
+
+  std::mutex m;
+  std::condition_variable cv;
+  size_t next = 0;        // next chunk that a mover takes
+  size_t queued = 0;      // chunks whose device copy is on the stream
+  size_t moved[kMaxBuffers] = {};  // per buffer: chunks the movers have moved through it
+  hipError_t err = hipSuccess;
+
+  bool upload() const { return kind == hipMemcpyHostToDevice; }
+  char* buffer(size_t c) const { return slab + c % buffers * chunk; }
   // fn(piece, offset in it, length, offset in the chunk) for the parts of chunk c
-  auto parts = [&](size_t c, auto&& fn) {
-    const size_t a = c * sh.chunk, b = std::min(total, a + sh.chunk);
+  template <typename Fn>
+  void parts(size_t c, Fn&& fn) const {
+    const size_t a = c * chunk, b = std::min(total, a + chunk);
     size_t base = 0;
     for (int i = 0; i < n; base += p[i++].bytes) {
       const size_t lo = std::max(a, base), hi = std::min(b, base + p[i].bytes);
       if (lo < hi) fn(p[i], lo - base, hi - lo, lo - a);
     }
-  };
-  auto buf = [&](int k) { return slab + (2 * w + k) * sh.chunk; };
-  auto fetch = [&](size_t c, int k) {
-    parts(c, [&](const HostPiece& q, size_t off, size_t len, size_t at) {
-      if (e == hipSuccess)
-        e = hipMemcpyAsync(buf(k) + at, static_cast<const char*>(q.src) + off, len,
-                           hipMemcpyDeviceToHost, s);
-    });
-    if (e == hipSuccess) e = hipEventRecord(ev_[2 * w + k], s);
-  };
-  const size_t chunks = (total + sh.chunk - 1) / sh.chunk;
-  int k = 0;
-  if (kind == hipMemcpyHostToDevice) {
-    for (size_t c = w; c < chunks && e == hipSuccess; c += sh.threads, k ^= 1) {
-      if (c >= (size_t)w + 2 * sh.threads) e = hipEventSynchronize(ev_[2 * w + k]);
-      if (e != hipSuccess) break;
-      parts(c, [&](const HostPiece& q, size_t off, size_t len, size_t at) {
-        std::memcpy(buf(k) + at, static_cast<const char*>(q.src) + off, len);
-        if (e == hipSuccess)
-          e = hipMemcpyAsync(static_cast<char*>(q.dst) + off, buf(k) + at, len, kind, s);
-      });
-      if (e == hipSuccess) e = hipEventRecord(ev_[2 * w + k], s);
-    }
-    return e;
   }
-  if ((size_t)w < chunks && e == hipSuccess) fetch(w, 0);
-  for (size_t c = w; c < chunks && e == hipSuccess; c += sh.threads, k ^= 1) {
-    if (c + sh.threads < chunks) fetch(c + sh.threads, k ^ 1);
-    if (e == hipSuccess) e = hipEventSynchronize(ev_[2 * w + k]);
-    if (e != hipSuccess) break;
-    parts(c, [&](const HostPiece& q, size_t off, size_t len, size_t at) {
-      std::memcpy(static_cast<char*>(q.dst) + off, buf(k) + at, len);
-    });
+  void fail(hipError_t e) {
+    std::lock_guard<std::mutex> lock(m);
+    if (err == hipSuccess) err = e;
+    cv.notify_all();
   }
-  return e;
-}
+  // Waits until ready() or an error; false after an error.
+  template <typename Fn>
+  bool wait(Fn&& ready) {
+    std::unique_lock<std::mutex> lock(m);
+    cv.wait(lock, [&] { return err != hipSuccess || ready(); });
+    return err == hipSuccess;
+  }
 
-hipError_t HostCopy::copy(const HostPiece* p, int n, hipMemcpyKind kind, int device,
-                          hipStream_t s) {
+  void move() {
+    for (;;) {
+      size_t c;
+      {
+        std::lock_guard<std::mutex> lock(m);
+        if (err != hipSuccess || next >= chunks) return;
+        c = next++;
+      }
+      // read-out: the chunk has arrived; upload: the buffer's last chunk has left
+      const size_t ahead = upload() ? (size_t)buffers : 0;
+      if (c >= ahead) {
+        if (!wait([&] { return queued > c - ahead; })) return;
+        const hipError_t e = hipEventSynchronize(ev[c % buffers]);
+        if (e != hipSuccess) return fail(e);
+      }
+      parts(c, [&](const HostPiece& q, size_t off, size_t len, size_t at) {
+        if (upload())
+          std::memcpy(buffer(c) + at, static_cast<const char*>(q.src) + off, len);
+        else
+          std::memcpy(static_cast<char*>(q.dst) + off, buffer(c) + at, len);
+      });
+      std::lock_guard<std::mutex> lock(m);
+      ++moved[c % buffers];
+      cv.notify_all();
+    }
+  }
+
+  void queue() {
+    for (size_t c = 0; c < chunks; ++c) {
+      // read-out: the buffer is free again; upload: it holds the chunk
+      const size_t uses = c / buffers + (upload() ? 1 : 0);
+      if (!wait([&] { return moved[c % buffers] >= uses; })) return;
+      hipError_t e = hipSuccess;
+      parts(c, [&](const HostPiece& q, size_t off, size_t len, size_t at) {
+        if (e != hipSuccess) return;
+        e = upload() ? hipMemcpyAsync(static_cast<char*>(q.dst) + off, buffer(c) + at, len, kind, s)
+                     : hipMemcpyAsync(buffer(c) + at, static_cast<const char*>(q.src) + off, len, kind, s);
+      });
+      if (e == hipSuccess) e = hipEventRecord(ev[c % buffers], s);
+      if (e != hipSuccess) return fail(e);
+      std::lock_guard<std::mutex> lock(m);
+      queued = c + 1;
+      cv.notify_all();
+    }
+  }
+};
+}  // namespace
+
+hipError_t HostCopy::copy(const HostPiece* p, int n, hipMemcpyKind kind, hipStream_t s) {
   size_t total = 0;
   for (int i = 0; i < n; ++i) total += p[i].bytes;
   const size_t mib = (size_t)1 << 20;
-  const Shape sh = total > 256 * mib ? Shape{6, 4 * mib}
-                                     : Shape{4, total > 16 * mib ? 2 * mib : mib};
+  const int movers = total > 256 * mib ? 6 : 4;
+  const size_t chunk = total > 256 * mib ? 4 * mib : (total > 16 * mib ? 2 * mib : mib);
+  const int buffers = 2 * movers;
+  std::thread th[kMaxBuffers / 2];
   Slab slab;
-  if (total <= 4 * mib || !events(2 * sh.threads) || !take(2 * sh.threads * sh.chunk, slab)) {
-    hipError_t e = hipSuccess;
-    for (int i = 0; i < n && e == hipSuccess; ++i)
-      e = hipMemcpyAsync(p[i].dst, p[i].src, p[i].bytes, kind, s);
-    const hipError_t es = hipStreamSynchronize(s);
-    return e != hipSuccess ? e : es;
+  if (total > 4 * mib && events(buffers) && take(buffers * chunk, slab)) {
+    Staging g{p, n, kind, s, slab.p, ev_, chunk, total, (total + chunk - 1) / chunk, buffers};
+    int started = 0;
+    try {
+      for (; started < movers; ++started) th[started] = std::thread([&g] { g.move(); });
+    } catch (...) {  // fewer threads
+    }
+    if (started) g.queue();
+    for (int i = 0; i < started; ++i) th[i].join();
+    // also after an error: nothing still uses the staging memory when it is given back
+    const hipError_t e = hipStreamSynchronize(s);
+    give(slab);
+    if (started) return g.err != hipSuccess ? g.err : e;
   }
-  hipError_t res[8];
-  std::thread th[8];
-  int started = 1;  // this thread takes lane 0, and the lanes that get no thread
-  try {
-    for (; started < sh.threads; ++started)
-      th[started] = std::thread([&, w = started] { res[w] = lane(w, sh, slab.p, p, n, total, kind, device, s); });
-  } catch (...) {
-  }
-  res[0] = lane(0, sh, slab.p, p, n, total, kind, device, s);
-  for (int w = started; w < sh.threads; ++w) res[w] = lane(w, sh, slab.p, p, n, total, kind, device, s);
-  for (int w = 1; w < started; ++w) th[w].join();
-  // also after an error: nothing still writes to the staging memory when it is given back
-  hipError_t e = hipStreamSynchronize(s);
-  give(slab);
-  for (int w = 0; w < sh.threads; ++w)
-    if (res[w] != hipSuccess) e = res[w];
-  return e;
+  hipError_t e = hipSuccess;
+  for (int i = 0; i < n && e == hipSuccess; ++i)
+    e = hipMemcpyAsync(p[i].dst, p[i].src, p[i].bytes, kind, s);
+  const hipError_t es = hipStreamSynchronize(s);
+  return e != hipSuccess ? e : es;
 }
 
 }  // namespace lbm

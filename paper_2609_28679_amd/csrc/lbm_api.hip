@@ -60,7 +60,6 @@ struct lbm_ctx {
   unsigned long long* mlp_cnt = nullptr;   // {fallbacks, updates}
   bool mlp_set = false;
   double mlp_tol = 0.0;
-  int device = 0;         // device the context was created on
   HostCopy host_copy;     // staging of large read-outs
   std::string err;
 };
@@ -445,7 +444,6 @@ int lbm_create(const lbm_params* p, const double* rho0, const double* u0, const 
       c->dp.full = true;
     }
   }
-  (void)hipGetDevice(&c->device);
   c->L = P.L;
   c->G = P.G;
   c->stream = static_cast<hipStream_t>(p->stream);
@@ -501,7 +499,7 @@ int lbm_create(const lbm_params* p, const double* rho0, const double* u0, const 
   double* const d_T0 = c->readout + (size_t)(1 + P.D) * nodes;
   const size_t field = (size_t)nodes * sizeof(double);
   const HostPiece init[3] = {{c->readout, rho0, field}, {c->readout + nodes, u0, P.D * field}, {d_T0, T0, field}};
-  if (e == hipSuccess) e = c->host_copy.copy(init, P.ddf ? 3 : 2, hipMemcpyHostToDevice, c->device, c->stream);
+  if (e == hipSuccess) e = c->host_copy.copy(init, P.ddf ? 3 : 2, hipMemcpyHostToDevice, c->stream);
   if (P.ddf) {
     // Fig. 1: f <- f^eq, g <- g^eq into B, then one collide-only pass B -> A so that A holds
     // the post-collision state of t = 0 (f* differs from f^eq when Phi is on)
@@ -700,7 +698,7 @@ int lbm_moments(lbm_ctx* c, double* rho, double* u, double* T, double* totals) {
   if (rho) out[pieces++] = {rho, d_rho, field};
   if (u) out[pieces++] = {u, d_u, c->D * field};
   if (T && c->ddf) out[pieces++] = {T, d_T, field};
-  HIP_TRY(c, c->host_copy.copy(out, pieces, hipMemcpyDeviceToHost, c->device, c->stream));
+  HIP_TRY(c, c->host_copy.copy(out, pieces, hipMemcpyDeviceToHost, c->stream));
   return LBM_OK;
 }
 
@@ -718,7 +716,7 @@ int lbm_populations(lbm_ctx* c, double* f, double* g) {
     else
       HIP_TRY(c, launch_decode_f(c->kind, c->D, i, c->A, c->L, view_of(c), c->p.wall_y != 0, c->readout, c->stream));
     const HostPiece out{dst, c->readout, nodes * sizeof(double)};
-    HIP_TRY(c, c->host_copy.copy(&out, 1, hipMemcpyDeviceToHost, c->device, c->stream));
+    HIP_TRY(c, c->host_copy.copy(&out, 1, hipMemcpyDeviceToHost, c->stream));
   }
   return LBM_OK;
 }

@@ -1,0 +1,114 @@
+"""The library's host layer (lbm_api, host_copy) on a fake device that runs on the CPU
+(host_fake.cpp): order of copies and launches, streams, devices, memory and failing launches."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2609_28679_amd import binding
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2609_28679_amd", "csrc")
+PER_THREAD = 2  # hipStreamPerThread
+STREAM = 0x1000  # any other handle
+ROCM = "/opt/rocm/include"
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(ROCM),
+                                reason="needs g++ and the HIP headers")
+
+
+@pytest.fixture(scope="module")
+def fake_lib(tmp_path_factory):
+    out = tmp_path_factory.mktemp("host") / "libhost.so"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-pthread", "-Wl,-Bsymbolic",
+                    "-D__HIP_PLATFORM_AMD__", "-isystem", ROCM, "-I", os.path.join(ROOT, "include"),
+                    "-I", CSRC, "-o", str(out), "-x", "c++", os.path.join(CSRC, "lbm_api.hip"),
+                    os.path.join(CSRC, "host_copy.hip"),
+                    os.path.join(ROOT, "tests", "host_fake.cpp")], check=True)
+    lib = ctypes.CDLL(str(out))
+    for name, (res, args) in binding.SIGNATURES.items():
+        if hasattr(lib, name):
+            getattr(lib, name).restype, getattr(lib, name).argtypes = res, args
+    lib.fake_uploaded.restype = ctypes.POINTER(ctypes.c_double)
+    lib.fake_foreign.restype = lib.fake_pins.restype = lib.fake_pinned_bytes.restype = ctypes.c_long
+    lib.fake_capture.argtypes = [ctypes.c_void_p, ctypes.c_int]
+    lib.fake_replay.argtypes = [ctypes.c_void_p]
+    lib.fake_malloc_limit.argtypes = [ctypes.c_size_t]
+    return lib
+
+
+@pytest.fixture
+def fake(fake_lib):
+    fake_lib.fake_reset()
+    return fake_lib
+
+
+class Context:
+    """One context of the library on the fake device; read-outs hold the steps of the state."""
+
+    def __init__(self, lib, shape=(64, 64), stream=STREAM, expect=binding.LBM_OK, **kw):
+        self.lib, self.shape = lib, shape
+        p = binding.LbmParams()
+        lib.lbm_default_params(ctypes.byref(p))
+        p.ny, p.nx = shape[-2:]
+        if len(shape) == 3:
+            p.lattice, p.nz = 1, shape[0]
+        p.stream = stream
+        for k, v in kw.items():
+            setattr(p, k, v)
+        self.D = len(shape)
+        self.rho = 1.0 + np.arange(np.prod(shape), dtype=np.float64).reshape(shape) * 1e-9
+        u = np.zeros((self.D,) + shape)
+        T = np.ones(shape)
+        self.ctx = ctypes.c_void_p()
+        rc = lib.lbm_create(ctypes.byref(p), binding._dptr(self.rho), binding._dptr(u),
+                            binding._dptr(T), ctypes.byref(self.ctx))
+        assert rc == expect, lib.lbm_last_error(None)
+
+    def step(self, n, expect=binding.LBM_OK):
+        assert self.lib.lbm_step(self.ctx, n) == expect
+
+    def moments(self, totals=False):
+        rho = np.full(self.shape, np.nan)
+        u = np.full((self.D,) + self.shape, np.nan)
+        t = np.empty(5)
+        rc = self.lib.lbm_moments(self.ctx, binding._dptr(rho), binding._dptr(u), None,
+                                  binding._dptr(t) if totals else None)
+        assert rc == binding.LBM_OK, self.lib.lbm_last_error(self.ctx)
+        out = np.concatenate([rho.ravel(), u.ravel()])
+        tag = (np.arange(out.size) % 4099) / 8192.0
+        steps = out - tag
+        assert np.all(steps == steps[0]), "values of several states, or out of place"
+        return int(steps[0])
+
+    def populations(self):
+        f = np.full((3 ** self.D,) + self.shape, np.nan)
+        assert self.lib.lbm_populations(self.ctx, binding._dptr(f), None) == binding.LBM_OK
+        n = f[0].size
+        steps = f.reshape(-1, n) - (np.arange(n) % 4099) / 8192.0 - 1000.0 * np.arange(len(f))[:, None]
+        assert np.all(steps == steps[0, 0])
+        return int(steps[0, 0])
+
+    def close(self):
+        self.lib.lbm_destroy(self.ctx)
+
+
+# 0.3, 5, 20 and 270 MB of fields
+@pytest.mark.parametrize("shape", [(100, 128), (401, 509), (1000, 833), (3307, 3400)])
+@pytest.mark.parametrize("stream", [STREAM, PER_THREAD, None])
+def test_copies_keep_the_order_of_the_callers_stream(fake, shape, stream):
+    """Everything that a copy puts on the caller's stream is put there by the calling thread: a
+    handle may mean another queue in another thread."""
+    c = Context(fake, shape, stream)
+    up = np.ctypeslib.as_array(fake.fake_uploaded(), (c.rho.size,))
+    assert np.array_equal(up, c.rho.ravel())
+    c.step(3)
+    assert c.moments() == 3
+    assert c.moments(totals=True) == 3
+    if shape[0] <= 1000:
+        assert c.populations() == 3
+    assert fake.fake_foreign() == 0
+    c.close()
