@@ -45,7 +45,7 @@ class HostCopy {
  private:
   static bool take(size_t bytes, Slab& slab);
   static void give(const Slab& slab);
-  bool events(int n);
+  bool events(int n, hipStream_t s);
   hipEvent_t ev_[kMaxBuffers];  // one per staging buffer
   int events_ = 0;
 };

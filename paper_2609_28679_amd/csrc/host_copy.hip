@@ -63,13 +63,21 @@ void HostCopy::give(const Slab& slab) {
   if (drop.p) (void)hipHostFree(drop.p);
 }
 
-bool HostCopy::events(int n) {
-  for (; events_ < n; ++events_)
-    if (hipEventCreateWithFlags(&ev_[events_], hipEventDisableTiming) != hipSuccess) {
-      (void)hipGetLastError();
-      return false;
-    }
-  return true;
+// An event belongs to the device that is current when it is made, which need not be the stream's:
+// a program with several GPUs may call with another one current, and keeps it.
+bool HostCopy::events(int n, hipStream_t s) {
+  if (events_ >= n) return true;
+  int device = 0, current = 0;
+  if (hipStreamGetDevice(s, &device) != hipSuccess || hipGetDevice(&current) != hipSuccess ||
+      (device != current && hipSetDevice(device) != hipSuccess)) {
+    (void)hipGetLastError();
+    return false;
+  }
+  while (events_ < n && hipEventCreateWithFlags(&ev_[events_], hipEventDisableTiming) == hipSuccess)
+    ++events_;
+  if (events_ < n) (void)hipGetLastError();
+  if (device != current) (void)hipSetDevice(current);
+  return events_ >= n;
 }
 
 namespace {
@@ -176,7 +184,7 @@ hipError_t HostCopy::copy(const HostPiece* p, int n, hipMemcpyKind kind, hipStre
   const int buffers = 2 * movers;
   std::thread th[kMaxBuffers / 2];
   Slab slab;
-  if (total > 4 * mib && events(buffers) && take(buffers * chunk, slab)) {
+  if (total > 4 * mib && events(buffers, s) && take(buffers * chunk, slab)) {
     Staging g{p, n, kind, s, slab.p, ev_, chunk, total, (total + chunk - 1) / chunk, buffers};
     int started = 0;
     try {

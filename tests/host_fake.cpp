@@ -93,6 +93,7 @@ int fake_step_launches() { return next_launches; }
 void fake_fail_step_launch(int k) { fail_in = k; }
 void fake_malloc_limit(size_t bytes) { malloc_limit = bytes; }
 int fake_current_device() { return current; }
+void fake_set_device(int d) { current = d; }
 const double* fake_uploaded() { return uploaded.data(); }
 void fake_capture(void* s, int on) { queue((hipStream_t)s).capturing = on != 0; }
 void fake_replay(void* s) {

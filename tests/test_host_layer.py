@@ -112,3 +112,17 @@ def test_copies_keep_the_order_of_the_callers_stream(fake, shape, stream):
         assert c.populations() == 3
     assert fake.fake_foreign() == 0
     c.close()
+
+
+def test_copies_leave_the_callers_device(fake):
+    """A program with several GPUs reads out a context of device 0 while device 1 is current."""
+    c = Context(fake, (401, 509))
+    fake.fake_set_device(1)
+    c.step(2)
+    assert c.moments() == 2 and c.populations() == 2
+    assert fake.fake_current_device() == 1
+    fresh = Context(fake, (1000, 833))  # its first copy, and so its events, with device 1 current
+    assert fresh.moments() == 0
+    assert fake.fake_current_device() == 1
+    c.close()
+    fresh.close()
