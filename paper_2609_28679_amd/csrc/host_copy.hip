@@ -175,16 +175,28 @@ struct Staging {
 };
 }  // namespace
 
+// Ordinary memory of the caller, which the device cannot reach by itself.
+static bool pageable(const void* host) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, host) == hipSuccess) return a.type == hipMemoryTypeUnregistered;
+  (void)hipGetLastError();
+  return true;
+}
+
 hipError_t HostCopy::copy(const HostPiece* p, int n, hipMemcpyKind kind, hipStream_t s) {
   size_t total = 0;
-  for (int i = 0; i < n; ++i) total += p[i].bytes;
+  bool stage = true;
+  for (int i = 0; i < n; ++i) {
+    total += p[i].bytes;
+    stage = stage && pageable(kind == hipMemcpyHostToDevice ? p[i].src : p[i].dst);
+  }
   const size_t mib = (size_t)1 << 20;
   const int movers = total > 256 * mib ? 6 : 4;
   const size_t chunk = total > 256 * mib ? 4 * mib : (total > 16 * mib ? 2 * mib : mib);
   const int buffers = 2 * movers;
   std::thread th[kMaxBuffers / 2];
   Slab slab;
-  if (total > 4 * mib && events(buffers, s) && take(buffers * chunk, slab)) {
+  if (stage && total > 4 * mib && events(buffers, s) && take(buffers * chunk, slab)) {
     Staging g{p, n, kind, s, slab.p, ev_, chunk, total, (total + chunk - 1) / chunk, buffers};
     int started = 0;
     try {

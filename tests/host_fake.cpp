@@ -35,7 +35,7 @@ std::map<char*, size_t> pinned;
 std::map<void*, size_t> allocated;
 std::vector<double> uploaded;
 std::thread::id home;  // the thread that calls the library
-long foreign = 0, pins = 0;
+long foreign = 0, pins = 0, copies = 0;
 int fail_in = 0, streams_device = 0, next_launches = 0;
 size_t malloc_limit = ~(size_t)0;
 thread_local int current = 0;
@@ -77,13 +77,14 @@ void fake_reset() {
   queues.clear();
   uploaded.clear();
   home = std::this_thread::get_id();
-  foreign = pins = 0;
+  foreign = pins = copies = 0;
   fail_in = next_launches = 0;
   streams_device = current = 0;
   malloc_limit = ~(size_t)0;
 }
 long fake_foreign() { return foreign; }
 long fake_pins() { return pins; }
+long fake_copies() { return copies; }
 long fake_pinned_bytes() {
   long b = 0;
   for (auto& r : pinned) b += (long)r.second;
@@ -131,6 +132,7 @@ hipError_t hipHostFree(void* p) {
 }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t st) {
   Lock lock(mu);
+  ++copies;
   put(st, [=] { std::memcpy(d, s, n); });
   const void* host = k == hipMemcpyHostToDevice ? s : d;
   Queue& q = queue(st);

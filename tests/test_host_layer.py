@@ -84,6 +84,9 @@ class Context:
         assert np.all(steps == steps[0]), "values of several states, or out of place"
         return int(steps[0])
 
+    def moments_into(self, rho, u):
+        return self.lib.lbm_moments(self.ctx, binding._dptr(rho), binding._dptr(u), None, None)
+
     def populations(self):
         f = np.full((3 ** self.D,) + self.shape, np.nan)
         assert self.lib.lbm_populations(self.ctx, binding._dptr(f), None) == binding.LBM_OK
@@ -126,3 +129,18 @@ def test_copies_leave_the_callers_device(fake):
     assert fake.fake_current_device() == 1
     c.close()
     fresh.close()
+
+
+def test_pinned_memory_of_the_caller_is_copied_directly(fake):
+    c = Context(fake, (1000, 833))
+    n = c.rho.size
+    p = ctypes.c_void_p()
+    fake.hipHostMalloc(ctypes.byref(p), ctypes.c_size_t(3 * n * 8), 0)
+    out = np.ctypeslib.as_array(ctypes.cast(p, binding._D), (3, n))
+    pins = fake.fake_pins()
+    copies = fake.fake_copies()
+    assert c.moments_into(out[0], out[1:]) == binding.LBM_OK
+    assert fake.fake_pins() == pins and fake.fake_copies() == copies + 2
+    assert np.array_equal(out[0], np.arange(n) % 4099 / 8192.0)
+    c.close()
+    fake.hipHostFree(p)
