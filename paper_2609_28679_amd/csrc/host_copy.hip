@@ -196,7 +196,8 @@ hipError_t HostCopy::copy(const HostPiece* p, int n, hipMemcpyKind kind, hipStre
   const int buffers = 2 * movers;
   std::thread th[kMaxBuffers / 2];
   Slab slab;
-  if (stage && total > 4 * mib && events(buffers, s) && take(buffers * chunk, slab)) {
+  if (stage && total > (kind == hipMemcpyHostToDevice ? 64 : 8) * mib && events(buffers, s) &&
+      take(buffers * chunk, slab)) {
     Staging g{p, n, kind, s, slab.p, ev_, chunk, total, (total + chunk - 1) / chunk, buffers};
     int started = 0;
     try {

@@ -99,7 +99,7 @@ class Context:
         self.lib.lbm_destroy(self.ctx)
 
 
-# 0.3, 5, 20 and 270 MB of fields
+# 0.3, 5, 20 and 270 MB of fields (uploads are staged from 64 MiB on)
 @pytest.mark.parametrize("shape", [(100, 128), (401, 509), (1000, 833), (3307, 3400)])
 @pytest.mark.parametrize("stream", [STREAM, PER_THREAD, None])
 def test_copies_keep_the_order_of_the_callers_stream(fake, shape, stream):
@@ -144,3 +144,20 @@ def test_pinned_memory_of_the_caller_is_copied_directly(fake):
     assert np.array_equal(out[0], np.arange(n) % 4099 / 8192.0)
     c.close()
     fake.hipHostFree(p)
+
+
+def test_contexts_made_one_at_a_time_pin_nothing_to_start(fake):
+    """Initial fields of 15 MB need no staging memory. A read-out pins one slab, which later ones
+    of any context use too, and the last context to go gives it back."""
+    shape = (700, 900)
+    for _ in range(3):
+        Context(fake, shape).close()
+    assert fake.fake_pins() == 0
+    a = Context(fake, shape)
+    assert a.moments() == 0 and fake.fake_pins() == 1
+    b = Context(fake, shape)
+    assert b.moments() == 0 and a.moments() == 0 and fake.fake_pins() == 1
+    a.close()
+    assert fake.fake_pinned_bytes() > 0
+    b.close()
+    assert fake.fake_pinned_bytes() == 0
