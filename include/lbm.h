@@ -121,8 +121,9 @@ typedef struct {
                           The choice changes memory use and speed, not the results. */
   double mlp_tol;      /* LBM_COLLIDE_MLP fallback threshold (see lbm_set_mlp) */
   void* stream;        /* hipStream_t for all work of this context; NULL = null stream */
-  void* workspace;     /* optional caller-owned device memory (>= lbm_workspace_size bytes,
-                          256-byte aligned); NULL: the library allocates and frees its own */
+  void* workspace;     /* optional caller-owned device memory (lbm_workspace_size bytes,
+                          256-byte aligned; see there for less); NULL: the library allocates
+                          and frees its own */
   size_t workspace_bytes;
 } lbm_params;
 
@@ -131,8 +132,13 @@ typedef struct {
    stream, no workspace. */
 void lbm_default_params(lbm_params* p);
 
-/* Device bytes the context needs for p (population buffers: one or two, reduction scratch,
-   diagnostics history). Returns LBM_EINVAL for invalid parameters. */
+/* Device bytes of a context for p (population buffers: one or two, reduction scratch,
+   diagnostics history, read-out area). Returns LBM_EINVAL for invalid parameters. Where the
+   one-buffer layout takes several steps per launch through the read-out area, that area is as
+   large as a state: 72 bytes per node instead of 40 for LBM_STORE_FP64, the padded rows for
+   small or ragged LBM_STORE_FP32 lattices. lbm_create also takes a workspace without this part
+   (and without the records of the lower windows of some D2Q9 DDF lattices, up to 26 KB) and then
+   runs one step per launch, with the same results. */
 int lbm_workspace_size(const lbm_params* p, size_t* bytes);
 
 /* Create a context and initialise the populations to the equilibrium of the initial fields

@@ -43,6 +43,7 @@
 #include "reduced_common.h"
 
 #include <algorithm>
+#include <climits>
 #include <cstdlib>
 #include <type_traits>
 
@@ -659,26 +660,30 @@ static Grid ddf_fill(Grid G, const Layout& L, int halo, int per_cu) {
   return G;
 }
 
-// Launch grid of one step, from the plan's grid: taller windows for the extended collisions.
-static Grid ddf_step_grid(Grid G, const Layout& L, int phi, int fmt, bool extended) {
+// Launch grid of one step, from the plan's grid: taller windows for the extended collisions. A step
+// that writes its diagnostics records keeps the plan's windows where the lower ones would write
+// more than there is room for.
+static Grid ddf_step_grid(Grid G, const Layout& L, int phi, int fmt, bool extended, int room) {
   if (fmt < 2 && extended && G.rows < kDdfExtRows) {
     G.rows = kDdfExtRows;
     fit_rows(G, L.ny);
   }
   const int halo = phi == 2 ? 2 : 1;
-  return ddf_fill(G, L, halo, fmt == 0 && halo == 1 && !extended ? 3 : 2);
+  const Grid filled = ddf_fill(G, L, halo, fmt == 0 && halo == 1 && !extended ? 3 : 2);
+  return filled.blocks() <= room ? filled : G;
 }
 
 int ddf_max_records(const Layout& L, const Grid& G, int phi, int fmt) {
-  return std::max(ddf_step_grid(G, L, phi, fmt, false).blocks(),
-                  ddf_step_grid(G, L, phi, fmt, true).blocks());
+  return std::max(ddf_step_grid(G, L, phi, fmt, false, INT_MAX).blocks(),
+                  ddf_step_grid(G, L, phi, fmt, true, INT_MAX).blocks());
 }
 
 hipError_t launch_ddf(int fmt, bool walls, bool pull, const void* A, void* B, const Layout& L,
                       const Grid& G0, const DdfParams& prm, float s_enc, float s_dec,
                       double* partials, void* nb, int* records, hipStream_t s) {
   if (prm.ext() && fmt >= 2) return hipErrorInvalidValue;  // no extended path with reduced storage
-  const Grid G = ddf_step_grid(G0, L, prm.phi, fmt, prm.ext() || prm.eos);
+  const Grid G = ddf_step_grid(G0, L, prm.phi, fmt, prm.ext() || prm.eos,
+                               partials && records ? *records : INT_MAX);
   if (records) *records = G.blocks();
   if (prm.neq) {
     if (fmt >= 2 || !walls || !nb || L.ny < 3 || prm.src) return hipErrorInvalidValue;

@@ -235,7 +235,10 @@ int validate(const lbm_params* p, std::string& why) {
   return LBM_OK;
 }
 
-void make_plan(const lbm_params* p, Plan& P) {
+// compact: the least memory that a context runs in. It leaves out what some lattices need for the
+// fastest steps alone, a read-out area as large as a state (several steps per launch in the in-place
+// layout) and records for lower windows (double distribution, D2Q9).
+void make_plan(const lbm_params* p, Plan& P, bool compact = false) {
   P.D = p->lattice == LBM_D2Q9 ? 2 : 3;
   P.Q = P.D == 2 ? 9 : 27;
   P.kind = p->storage == LBM_STORE_FP64 ? 1 : 0;
@@ -255,7 +258,7 @@ void make_plan(const lbm_params* p, Plan& P) {
   else
     P.G = make_grid(P.L);
   P.partial_slots = std::max(P.G.blocks(), 1024);
-  if (P.ddf && P.D == 2)  // small lattices and extended collisions have their own windows
+  if (P.ddf && P.D == 2 && !compact)  // small lattices and extended collisions have their own windows
     P.partial_slots = std::max(P.partial_slots,
                                ddf_max_records(P.L, P.G, p->phi, P.codec >= 0 ? 2 + P.codec : P.kind));
   if (P.ddf && P.D == 3)  // the one-launch step and the upwind sweeps have their own grids
@@ -285,6 +288,7 @@ void make_plan(const lbm_params* p, Plan& P) {
   // which holds nothing between calls (40 bytes per node against 36 of the float32 state), and
   // back (see multi_launches).
   const size_t readout = (size_t)P.L.nodes() * (P.D + 3) * 8;
+  if (P.aa && pop > readout && compact) P.multi = false;
   P.off_read = off; off = align_up(off + (P.aa && P.multi ? std::max(readout, pop) : readout), 256);
   // surrogate region: 16 bytes of 64-bit counters (8-byte aligned for the atomics), then the
   // weights 256 bytes further
@@ -373,9 +377,10 @@ int lbm_create(const lbm_params* p, const double* rho0, const double* u0, const 
   int rc = validate(p, why);
   if (rc) return fail(nullptr, rc, why);
   if (!rho0 || !u0) return fail(nullptr, LBM_EINVAL, "rho0 and u0 are required");
-  Plan P;
+  Plan P, least;
   make_plan(p, P);
-  if (!plan_aligned(P)) return fail(nullptr, LBM_EINVAL, "internal: misaligned workspace plan");
+  make_plan(p, least, true);
+  if (!plan_aligned(P) || !plan_aligned(least)) return fail(nullptr, LBM_EINVAL, "internal: misaligned workspace plan");
   if (P.ddf && !T0) return fail(nullptr, LBM_EINVAL, "the double-distribution model needs T0");
   const int64_t nodes = P.L.nodes();
   // host-side admissibility of the initial state
@@ -454,13 +459,13 @@ int lbm_create(const lbm_params* p, const double* rho0, const double* u0, const 
   c->F_state = c->F;
   c->heat = c->heat_state = p->heat_source;
   sync_sources(c);
-  c->partial_slots = P.partial_slots;
   auto cleanup_fail = [&](int code) {
     std::string m = c->err;
     lbm_destroy(c);
     return fail(nullptr, code, m);
   };
   if (p->workspace) {
+    if (p->workspace_bytes < P.total) P = least;
     if (p->workspace_bytes < P.total) {
       c->err = "workspace too small: need " + std::to_string(P.total) + " bytes";
       return cleanup_fail(LBM_ENOMEM);
@@ -470,6 +475,11 @@ int lbm_create(const lbm_params* p, const double* rho0, const double* u0, const 
   } else {
     hipError_t e = hipMalloc(&c->ws, P.total);
     if (e != hipSuccess) {
+      (void)hipGetLastError();
+      P = least;
+      e = hipMalloc(&c->ws, P.total);
+    }
+    if (e != hipSuccess) {
       c->ws = nullptr;
       c->err = std::string("hipMalloc of ") + std::to_string(P.total) + " bytes: " + hipGetErrorString(e);
       return cleanup_fail(LBM_ENOMEM);
@@ -477,6 +487,7 @@ int lbm_create(const lbm_params* p, const double* rho0, const double* u0, const 
     c->own_ws = true;
   }
   c->ws_bytes = P.total;
+  c->partial_slots = P.partial_slots;
   c->A = c->ws + P.off_A;
   c->multi = P.multi;
   c->pair3 = !P.ddf && P.D == 3 && !P.aa && P.kind == 0 && !p->wall_y && p->nx <= 1 << 24;
@@ -588,9 +599,10 @@ int lbm_step(lbm_ctx* c, int64_t n) {
       e = launch_bgk_d2q9_mlp(c->A, c->B, c->L, c->G, c->omega, c->p.wall_y != 0, c->mlp_w, c->mlp_tol, c->mlp_cnt, part, c->stream);
     } else if (c->ddf && c->D == 3)
       e = launch_ddf3(c->kind, c->p.wall_y != 0, true, c->A, c->B, c->L, c->G, c->dp, c->fld, c->nb, part, &records, c->stream);
-    else if (c->ddf)
+    else if (c->ddf) {
+      records = c->partial_slots;
       e = launch_ddf(c->fmt, c->p.wall_y != 0, true, c->A, c->B, c->L, c->G, c->dp, c->s_enc, c->s_dec, part, c->nb, &records, c->stream);
-    else if (c->codec >= 0)
+    } else if (c->codec >= 0)
       e = launch_bgk_d2q9_red(c->codec, c->A, c->B, c->L, c->G, c->omega, c->p.wall_y != 0, c->s_enc, c->s_dec, part, c->stream);
     else if (c->aa && c->D == 2)
       e = launch_bgk_d2q9_aa(c->kind, (c->t & 1) != 0, c->A, c->L, c->G, c->omega, c->F, c->p.wall_y != 0, part, c->stream);

@@ -135,8 +135,9 @@ Grid make_grid_ddf(const Layout& L, int halo, bool reduced);
 hipError_t launch_ddf_rest_state(const DdfParams& prm, double* out, hipStream_t s);
 // nb: boundary-row buffer of the non-equilibrium extrapolation walls (2 x 18 rows of `pitch`
 // storage elements; used when prm.neq, NULL otherwise).
-// records: set to the number of per-workgroup diagnostics records the step writes to partials
-// (at most ddf_max_records; may be NULL).
+// records: in, the per-workgroup diagnostics records that partials has room for (the plan grid's, or
+// ddf_max_records for the fastest windows at every size); out, the number the step writes. May be
+// NULL.
 hipError_t launch_ddf(int fmt, bool walls, bool pull, const void* A, void* B, const Layout& L,
                       const Grid& G, const DdfParams& prm, float s_enc, float s_dec,
                       double* partials, void* nb, int* records, hipStream_t s);

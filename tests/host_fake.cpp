@@ -36,7 +36,7 @@ std::map<void*, size_t> allocated;
 std::vector<double> uploaded;
 std::thread::id home;  // the thread that calls the library
 long foreign = 0, pins = 0, copies = 0;
-int fail_in = 0, streams_device = 0, next_launches = 0;
+int record_room = 0, fail_in = 0, streams_device = 0, next_launches = 0;
 size_t malloc_limit = ~(size_t)0;
 thread_local int current = 0;
 
@@ -90,6 +90,7 @@ long fake_pinned_bytes() {
   for (auto& r : pinned) b += (long)r.second;
   return b;
 }
+int fake_record_room() { return record_room; }
 int fake_step_launches() { return next_launches; }
 void fake_fail_step_launch(int k) { fail_in = k; }
 void fake_malloc_limit(size_t bytes) { malloc_limit = bytes; }
@@ -238,6 +239,7 @@ hipError_t launch_bgk_d3q27_pair(const void* A, void* B, const Layout&, double, 
 hipError_t launch_bgk_d2q9_red(int, const void* A, void* B, const Layout&, const Grid&, double, bool, float, float, double*, hipStream_t s) { return take(A, B, 1, s); }
 hipError_t launch_bgk_d2q9_mlp(const void* A, void* B, const Layout&, const Grid&, double, bool, const float*, double, unsigned long long*, double*, hipStream_t s) { return take(A, B, 1, s); }
 hipError_t launch_ddf(int, bool, bool pull, const void* A, void* B, const Layout&, const Grid&, const DdfParams&, float, float, double*, void*, int* records, hipStream_t s) {
+  if (records) record_room = *records;
   if (records) *records = 32;
   return pull ? take(A, B, 1, s) : put(s, [=] { count(B) = count(A); });
 }

@@ -161,3 +161,59 @@ def test_contexts_made_one_at_a_time_pin_nothing_to_start(fake):
     assert fake.fake_pinned_bytes() > 0
     b.close()
     assert fake.fake_pinned_bytes() == 0
+
+
+def _workspace_size(lib, shape, **kw):
+    p = binding.LbmParams()
+    lib.lbm_default_params(ctypes.byref(p))
+    p.ny, p.nx = shape
+    for k, v in kw.items():
+        setattr(p, k, v)
+    n = ctypes.c_size_t(0)
+    assert lib.lbm_workspace_size(ctypes.byref(p), ctypes.byref(n)) == 0
+    return n.value
+
+
+def _up(n):
+    return (n + 255) // 256 * 256
+
+
+@pytest.mark.parametrize("storage,elem", [("fp32", 4), ("fp64", 8)])
+def test_workspace_without_room_for_several_steps_per_launch(fake, storage, elem):
+    """A caller's workspace that holds one state and the read-out area is accepted, as is device
+    memory of that size; the run takes one step per launch."""
+    shape = (40, 65)
+    kw = dict(storage=binding.STORAGES[storage])
+    full = _workspace_size(fake, shape, **kw)
+    least = full - (_up(9 * 128 * 40 * elem) - _up(5 * 65 * 40 * 8))
+    buf = ctypes.create_string_buffer(full + 256)
+    base = (ctypes.addressof(buf) + 255) // 256 * 256
+    for size, launches in ((full, 3), (full - 1, 13), (least, 13)):
+        c = Context(fake, shape, workspace=base, workspace_bytes=size, **kw)
+        before = fake.fake_step_launches()
+        c.step(13)
+        assert fake.fake_step_launches() - before == launches
+        assert c.moments() == 13 and c.populations() == 13
+        c.close()
+    Context(fake, shape, expect=binding.LBM_ENOMEM, workspace=base, workspace_bytes=least - 1, **kw)
+    fake.fake_malloc_limit(full - 1)
+    c = Context(fake, shape, **kw)
+    c.step(13)
+    assert c.moments() == 13
+    c.close()
+    fake.fake_malloc_limit(least - 1)
+    Context(fake, shape, expect=binding.LBM_ENOMEM, **kw)
+
+
+def test_workspace_with_records_of_the_plans_windows(fake):
+    """2000 records for the lower windows of this fake's lattices, 1024 for the plan's own."""
+    shape = (40, 65)
+    full = _workspace_size(fake, shape, model=1)
+    least = full - (_up(2000 * 40) - _up(1024 * 40))
+    buf = ctypes.create_string_buffer(full + 256)
+    base = (ctypes.addressof(buf) + 255) // 256 * 256
+    for size, room in ((full, 2000), (least, 1024)):
+        c = Context(fake, shape, model=1, phi=2, diag_every=1, workspace=base, workspace_bytes=size)
+        c.step(5)
+        assert fake.fake_record_room() == room and c.moments() == 5
+        c.close()
