@@ -151,9 +151,12 @@ int lbm_workspace_size(const lbm_params* p, size_t* bytes);
 int lbm_create(const lbm_params* p, const double* rho0, const double* u0, const double* T0,
                lbm_ctx** out);
 
-/* Advance n >= 0 time steps (one fused pull stream-collide kernel launch per step), enqueued
-   asynchronously on the context stream. With diag_every > 0 the call synchronises once at its
-   end and returns LBM_EUNSTABLE if any totals recorded during the call are non-finite. */
+/* Advance n >= 0 time steps, enqueued asynchronously on the context stream: fused stream-collide
+   kernel launches of one step each or, where the configuration allows, of several (the results
+   are the same, bit for bit). With diag_every > 0 the call synchronises once at its end and
+   returns LBM_EUNSTABLE if any totals recorded during the call are non-finite.
+   May be captured into a graph where it records no totals: for even n every replay advances the
+   state by n steps (lbm_time counts the captured call once). */
 int lbm_step(lbm_ctx* ctx, int64_t n);
 
 /* Replace the uniform body force (force[3], as lbm_params.force) for the collisions of the

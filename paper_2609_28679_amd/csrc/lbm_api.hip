@@ -286,7 +286,7 @@ void make_plan(const lbm_params* p, Plan& P, bool compact = false) {
   P.off_hist = off; off = align_up(off + (size_t)kHistoryCap * 6 * 8, 256);
   // The in-place layout has no second buffer: several steps per launch go to the read-out area,
   // which holds nothing between calls (40 bytes per node against 36 of the float32 state), and
-  // back (see multi_launches).
+  // back (see make_batch).
   const size_t readout = (size_t)P.L.nodes() * (P.D + 3) * 8;
   if (P.aa && pop > readout && compact) P.multi = false;
   P.off_read = off; off = align_up(off + (P.aa && P.multi ? std::max(readout, pop) : readout), 256);
@@ -314,13 +314,40 @@ bool plan_aligned(const Plan& P) {
   return true;
 }
 
-// Launches that take `left` (even) steps, up to kMultiSteps each, from one buffer into the other.
-// In the in-place layout (aa) the second buffer is the read-out area and the state has to end in
-// its own, so their number is even: none for fewer than four steps.
-int64_t multi_launches(bool aa, int64_t left) {
-  const int64_t m = (left + kMultiSteps - 1) / kMultiSteps;
-  if (!aa || m % 2 == 0) return m;
-  return left >= 4 ? m + 1 : 0;
+// Steps that one launch of the context takes from one buffer into the other (0: one-step kernels
+// only). In the in-place layout the state has to be at an even step count.
+int batch_steps(const lbm_ctx* c) {
+  if (c->multi) return c->aa && (c->t & 1) ? 0 : kMultiSteps;
+  if (c->pair3) return c->F.on() ? 0 : 2;
+  return c->ddf && c->D == 2 && ddf_pair_supported(c->fmt, c->L, c->dp) ? 2 : 0;
+}
+
+// Launches of up to `most` steps each that take an even number of the next `ahead` steps. keep: the
+// state has to end in the buffer it began in, so their number is even too: in the in-place layout,
+// whose second buffer is the read-out area, and in a captured call, which takes the same buffers
+// each time it is replayed.
+struct Batch {
+  int64_t launches, steps;
+};
+Batch make_batch(int most, bool keep, int64_t ahead) {
+  Batch b{0, ahead & ~(int64_t)1};
+  b.launches = (b.steps + most - 1) / most;
+  if (keep && b.launches % 2) {
+    if (b.steps >= 2 * (b.launches + 1)) {
+      ++b.launches;
+    } else {
+      --b.launches;
+      b.steps = b.launches * most;
+    }
+  }
+  return b;
+}
+
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (!s) return false;  // the null stream cannot be captured
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
+  return st != hipStreamCaptureStatusNone;
 }
 
 // Layout of the stored state for the read-out kernels: -1 two buffers, else the parity of t.
@@ -553,41 +580,31 @@ int lbm_step(lbm_ctx* c, int64_t n) {
   if (n < 0) return fail(c, LBM_EINVAL, "n must be >= 0");
   const int de = c->p.diag_every;
   const int64_t hist_before = c->hist_written;
+  const bool keep = c->aa || capturing(c->stream);
   for (int64_t k = 0; k < n; ++k) {
-    if (c->multi && !(c->aa && (c->t & 1))) {
+    if (const int most = batch_steps(c)) {
       // the steps up to the next diagnostics entry, whose step sums its own moments
       int64_t ahead = n - k;
       if (de > 0) ahead = std::min(ahead, de - 1 - c->t % de);
-      int64_t left = ahead & ~(int64_t)1;
-      for (int64_t m = multi_launches(c->aa, left); m > 0; --m) {
-        const int T = (int)(2 * ((left / 2 + m - 1) / m));
-        HIP_TRY(c, launch_bgk_d2q9_multi(c->kind, c->A, c->B, c->L, c->aa, c->omega, c->F, c->p.wall_y != 0, T, c->stream));
+      Batch b = make_batch(most, keep, ahead);
+      for (; b.launches > 0; --b.launches) {
+        const int T = (int)(2 * ((b.steps / 2 + b.launches - 1) / b.launches));
+        hipError_t e;
+        if (c->multi)
+          e = launch_bgk_d2q9_multi(c->kind, c->A, c->B, c->L, c->aa, c->omega, c->F, c->p.wall_y != 0, T, c->stream);
+        else if (c->pair3)
+          e = launch_bgk_d3q27_pair(c->A, c->B, c->L, c->omega, c->stream);
+        else
+          e = launch_ddf_pair(c->fmt, c->p.wall_y != 0, c->A, c->B, c->L, c->dp, c->stream);
+        if (e != hipSuccess) return hip_fail(c, e, "step kernel launch");
         std::swap(c->A, c->B);
         c->t += T;
         k += T;
-        left -= T;
+        b.steps -= T;
         c->F_state = c->F;
+        c->heat_state = c->heat;
       }
       if (k >= n) break;
-    }
-    if (c->pair3 && !c->F.on() && n - k >= 2 && (de == 0 || c->t % de < de - 2)) {
-      HIP_TRY(c, launch_bgk_d3q27_pair(c->A, c->B, c->L, c->omega, c->stream));
-      std::swap(c->A, c->B);
-      c->t += 2;
-      ++k;
-      c->F_state = c->F;
-      continue;
-    }
-    if (c->ddf && c->D == 2 && n - k >= 2 && ddf_pair_supported(c->fmt, c->L, c->dp) &&
-        (de == 0 || c->t % de < de - 2)) {
-      // two steps in one launch, neither of them a diagnostics entry
-      HIP_TRY(c, launch_ddf_pair(c->fmt, c->p.wall_y != 0, c->A, c->B, c->L, c->dp, c->stream));
-      std::swap(c->A, c->B);
-      c->t += 2;
-      ++k;
-      c->F_state = c->F;
-      c->heat_state = c->heat;
-      continue;
     }
     const int64_t tn = c->t + 1;
     const bool diag = de > 0 && tn % de == 0;

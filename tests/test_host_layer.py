@@ -217,3 +217,40 @@ def test_workspace_with_records_of_the_plans_windows(fake):
         c.step(5)
         assert fake.fake_record_room() == room and c.moments() == 5
         c.close()
+
+
+MODELS = {"d2q9": ((40, 65), {}), "d2q9_two": ((40, 65), dict(streaming=1)),
+          "d3q27_two": ((6, 10, 20), dict(streaming=1)), "ddf": ((40, 65), dict(model=1)),
+          "bf16": ((40, 65), dict(storage=1))}
+
+
+@pytest.mark.parametrize("model", sorted(MODELS))
+@pytest.mark.parametrize("n", [2, 4, 6, 8, 10, 12, 14, 18, 20, 26])
+def test_replays_of_a_captured_call_advance_the_state(fake, model, n):
+    shape, kw = MODELS[model]
+    for before in (0, 2, 6, 7):
+        fake.fake_reset()
+        c = Context(fake, shape, **kw)
+        c.step(before)
+        fake.fake_capture(STREAM, 1)
+        c.step(n)
+        fake.fake_capture(STREAM, 0)
+        assert c.moments() == before  # captured, not run
+        for k in range(1, 4):
+            fake.fake_replay(STREAM)
+            assert c.moments() == before + k * n, (before, k)
+        c.close()
+
+
+@pytest.mark.parametrize("model", sorted(MODELS))
+def test_calls_take_their_steps(fake, model):
+    """Any cutting of a run into calls, with and without diagnostics entries."""
+    shape, kw = MODELS[model]
+    for every in (0, 1, 2, 3, 4, 7):
+        c = Context(fake, shape, diag_every=every, **kw)
+        t = 0
+        for n in (1, 2, 3, 5, 6, 7, 0, 12, 13, 25, 4, 40):
+            c.step(n)
+            t += n
+            assert c.moments() == t, (every, n)
+        c.close()
