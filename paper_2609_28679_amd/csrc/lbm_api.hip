@@ -343,6 +343,15 @@ Batch make_batch(int most, bool keep, int64_t ahead) {
   return b;
 }
 
+// After a launch that failed between two of the in-place layout: the state back from the read-out
+// area, which the next read-out writes, into its own buffer.
+void state_home(lbm_ctx* c) {
+  if (!c->aa || c->A != static_cast<void*>(c->readout)) return;
+  const size_t state = (size_t)c->planes * c->L.plane * (c->kind ? 8 : 4);
+  if (hipMemcpyAsync(c->B, c->A, state, hipMemcpyDeviceToDevice, c->stream) == hipSuccess)
+    std::swap(c->A, c->B);
+}
+
 bool capturing(hipStream_t s) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (!s) return false;  // the null stream cannot be captured
@@ -596,7 +605,10 @@ int lbm_step(lbm_ctx* c, int64_t n) {
           e = launch_bgk_d3q27_pair(c->A, c->B, c->L, c->omega, c->stream);
         else
           e = launch_ddf_pair(c->fmt, c->p.wall_y != 0, c->A, c->B, c->L, c->dp, c->stream);
-        if (e != hipSuccess) return hip_fail(c, e, "step kernel launch");
+        if (e != hipSuccess) {
+          state_home(c);
+          return hip_fail(c, e, "step kernel launch");
+        }
         std::swap(c->A, c->B);
         c->t += T;
         k += T;

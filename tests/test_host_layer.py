@@ -254,3 +254,21 @@ def test_calls_take_their_steps(fake, model):
             t += n
             assert c.moments() == t, (every, n)
         c.close()
+
+
+@pytest.mark.parametrize("model", sorted(MODELS))
+@pytest.mark.parametrize("k", [1, 2, 3])
+def test_failing_launch_leaves_a_state_that_can_be_read(fake, model, k):
+    """The k-th launch of a call fails: the context stands at the steps taken until then."""
+    shape, kw = MODELS[model]
+    c = Context(fake, shape, **kw)
+    fake.fake_fail_step_launch(k)
+    c.step(24, expect=binding.LBM_EDEVICE)
+    t = ctypes.c_int64(0)
+    assert fake.lbm_time(c.ctx, ctypes.byref(t)) == 0
+    for _ in range(2):
+        assert c.moments() == t.value
+    assert c.populations() == t.value
+    c.step(7)
+    assert c.moments() == t.value + 7
+    c.close()
