@@ -589,7 +589,7 @@ int lbm_step(lbm_ctx* c, int64_t n) {
   if (n < 0) return fail(c, LBM_EINVAL, "n must be >= 0");
   const int de = c->p.diag_every;
   const int64_t hist_before = c->hist_written;
-  const bool keep = c->aa || capturing(c->stream);
+  const bool keep = c->aa || (n > 1 && capturing(c->stream));
   for (int64_t k = 0; k < n; ++k) {
     if (const int most = batch_steps(c)) {
       // the steps up to the next diagnostics entry, whose step sums its own moments

@@ -292,8 +292,9 @@ k_mlp_grad(const float* __restrict__ X, const float* __restrict__ T, int64_t n, 
   for (int j = 0; j < 4; ++j)
     if (4 * q + j < kOut) out[oW3 + (4 * q + j) * kHid + 16 * wv + r] = d3[j];
   // biases: samples 16 apart added in order, then over the 16 lanes of a row. Which products are
-  // rounded before they are added follows the trainings this kernel has to reproduce (see
-  // gelu_derivative); either choice is within an ulp of the other.
+  // rounded before they are added (the second layer's, but for units 0, 4, 8 and 12) keeps the
+  // results of trainings: either choice is within an ulp of the other, but not after some hundred
+  // Adam steps (see gelu_derivative). tests/test_gpu_mlp_pinned.py holds a stored training.
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int h = 16 * wv + 4 * q + j;
