@@ -8,13 +8,11 @@
 // kernels -> this one: float32 64^2 2.54 -> 0.99 (launches), 2048^2 44.2 -> 24.3, 4096^2 210 ->
 // 86.7; float64 1001 x 515 11.3 -> 5.1, 2048^2 97.2 -> 39.4.
 #include "bgk_common.h"
-
-#include <algorithm>
+#include "routes.h"
 
 namespace lbm {
 
 constexpr int kMsLanes = 64;  // region columns: one per lane
-constexpr int kCus = 256;     // compute units
 
 // T steps of k_bgk_d2q9 (T even), from state A to state B. A workgroup owns `rows` rows of
 // 64 - 2 (T - 1) columns; its region is the owned rectangle and T - 1 nodes more on every side,

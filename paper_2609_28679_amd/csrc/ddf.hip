@@ -41,10 +41,9 @@
 // Arithmetic is float64.
 #include "ddf_common.h"
 #include "reduced_common.h"
+#include "routes.h"
 
-#include <algorithm>
 #include <climits>
-#include <cstdlib>
 #include <type_traits>
 
 namespace lbm {
@@ -495,26 +494,6 @@ __global__ void k_ddf_rest_state(DdfParams prm, double* __restrict__ out) {
 }
 
 // ---- launchers ------------------------------------------------------------------------------
-Grid make_grid_ddf(const Layout& L, int halo, bool reduced) {
-  Grid G;
-  G.bx = kBlock;
-  // own columns per workgroup: kBlock - 2 halo, less one staging-only thread per side when
-  // the rows are staged (the kernel's TXI)
-  const int txi = kBlock - 2 * halo - (reduced ? 2 : 0);
-  G.nbx = (L.nx + txi - 1) / txi;
-  // rows per workgroup from sweeps on MI355X at 4096^2 with walls (float32, central Phi:
-  // 2 -> 588 us, 4 -> 553, 8 -> 580, 16 -> 599; float32, upwind Phi: 4 -> 646, 8 -> 596,
-  // 16 -> 586; reduced bf16: 8 -> 676, 16 -> 602, 32 -> 604): short windows give more
-  // workgroups in flight, taller ones amortise the halo rows (two per side for the upwind
-  // stencil) and the staged kernel's 2-row staging halo
-  G.rows = reduced ? 16 : (halo == 2 ? 16 : 4);
-#ifdef LBM_TUNING_ENV
-  if (const char* v = getenv("LBM_DDF_ROWS")) G.rows = atoi(v);
-#endif
-  fit_rows(G, L.ny);
-  return G;
-}
-
 template <class IO, int HALO, int WALLS, bool PULL, int EXT>
 static void ddf_launch_s(const IO& io, const Layout& L, const Grid& G, const DdfParams& prm,
                          double* partials, hipStream_t s) {
@@ -628,54 +607,6 @@ k_ddf_neq_rows(const S* __restrict__ A, int nx, int ny, int64_t pitch, int64_t p
     nb[(side * 18 + i) * pitch + x] = (S)(feB[i] + (f[i] - feN[i]) - prm.wf[i]);
     nb[(side * 18 + 9 + i) * pitch + x] = (S)(geB[i] + (g[i] - geN[i]) - prm.wg[i]);
   }
-}
-
-// Rows per workgroup of the extended collisions (sources, transport control, van der Waals):
-// their longer per-row arithmetic favours taller windows than the plain step's. Measured at
-// 4096^2 with walls, central Phi, float32 (4 / 6 / 8 / 10 rows): sources 618 / 589 / 582 /
-// 583 us, Pr 0.71 646 / 613 / 601 / 599, van der Waals 719 / 673 / 649 / 644; the plain and NEQ
-// steps keep their 4 (552 / 568 at 6 and 561 / 580).
-constexpr int kDdfExtRows = 8;
-
-// Lattices that do not fill the chip several times over get lower windows: the rows in
-// [1, G.rows] that take the least window rows in turn, rounds of resident workgroups x (rows + 2
-// halo + 1 for the start). Three workgroups fit a compute unit for the plain float32 step with
-// central Phi, two otherwise. us per step, the fixed rows -> these: 64^2 plain 9.6 -> 5.9, upwind
-// 28.1 -> 7.9, float16 44.6 -> 11.5, Pr 0.71 with NEQ walls 21.9 -> 10.5; 512^2 plain 16.0 ->
-// 13.8, upwind 38.5 -> 22; 1021 x 509 Pr 0.71 with NEQ walls 38.3 -> 30.6, float16 48.7 -> 32.
-static Grid ddf_fill(Grid G, const Layout& L, int halo, int per_cu) {
-  const int64_t slots = 256 * per_cu;
-  int64_t best = -1;
-  int rows = G.rows;
-  for (int r = 1; r <= G.rows; ++r) {
-    const int64_t blocks = (int64_t)G.nbx * ((L.ny + r - 1) / r);
-    const int64_t cost = (blocks + slots - 1) / slots * (r + 2 * halo + 1);
-    if (best < 0 || cost <= best) {
-      best = cost;
-      rows = r;
-    }
-  }
-  G.rows = rows;
-  fit_rows(G, L.ny);
-  return G;
-}
-
-// Launch grid of one step, from the plan's grid: taller windows for the extended collisions. A step
-// that writes its diagnostics records keeps the plan's windows where the lower ones would write
-// more than there is room for.
-static Grid ddf_step_grid(Grid G, const Layout& L, int phi, int fmt, bool extended, int room) {
-  if (fmt < 2 && extended && G.rows < kDdfExtRows) {
-    G.rows = kDdfExtRows;
-    fit_rows(G, L.ny);
-  }
-  const int halo = phi == 2 ? 2 : 1;
-  const Grid filled = ddf_fill(G, L, halo, fmt == 0 && halo == 1 && !extended ? 3 : 2);
-  return filled.blocks() <= room ? filled : G;
-}
-
-int ddf_max_records(const Layout& L, const Grid& G, int phi, int fmt) {
-  return std::max(ddf_step_grid(G, L, phi, fmt, false, INT_MAX).blocks(),
-                  ddf_step_grid(G, L, phi, fmt, true, INT_MAX).blocks());
 }
 
 hipError_t launch_ddf(int fmt, bool walls, bool pull, const void* A, void* B, const Layout& L,

@@ -25,13 +25,11 @@
 // The state between the steps is rounded to float32 like a stored one and the arithmetic rounds like
 // the one-step kernel's, so the results are those of two launches of it, bit for bit.
 #include "ddf_common.h"
+#include "routes.h"
 
-#include <algorithm>
 #include <type_traits>
 
 namespace lbm {
-
-constexpr int kPairHalo = 3;  // columns per side that only supply neighbours
 
 template <typename S, int WALLS, int EXT>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EXT == 0 && WALLS != 2 ? 2 : 1)))
@@ -283,50 +281,27 @@ k_ddf_pair(const S* __restrict__ A, S* __restrict__ B, int nx, int ny, int64_t p
 }
 
 // ---- launcher -------------------------------------------------------------------------------
-// Taken from about 700 000 nodes on (NEQ walls: 400 000): a window row costs more serial time
-// here than in the one-step kernel, which smaller lattices show; larger ones are bound by memory
-// traffic, which this kernel halves. us per step, one step / two per launch: 512^2 plain 13.8 /
-// 19.4, Pr 0.71 with NEQ walls 23.3 / 23.9; 1021 x 509 plain 24.3 / 25.1, plain with NEQ walls
-// 27.8 / 23.1, Pr 0.71 with NEQ walls 30.6 / 28.3; 1024^2 plain 44 / 38.
-bool ddf_pair_supported(int fmt, const Layout& L, const DdfParams& prm) {
-  return fmt == 0 && prm.phi != 2 && L.nx <= 1 << 24 && L.nodes() >= (prm.neq ? 400000 : 700000);
-}
-
 template <typename S, int WALLS>
-static void pair_launch(const S* A, S* B, const Layout& L, const DdfParams& prm, hipStream_t s) {
-  const int nt = std::min(kBlock, (L.nx + 2 * kPairHalo + 63) / 64 * 64);
-  const int nbx = (L.nx + nt - 2 * kPairHalo - 1) / (nt - 2 * kPairHalo);
-  const int64_t slots = 256 * (int64_t)(prm.ext() || prm.eos || prm.neq ? 1 : 2) * kBlock / nt;
-  int rows = 1;
-  int64_t best = -1;
-  const int max_rows = std::min(L.ny, 512);
-  for (int r = 1; r <= max_rows; ++r) {
-    const int64_t blocks = (int64_t)nbx * ((L.ny + r - 1) / r);
-    const int64_t cost = (blocks + slots - 1) / slots * (r + 8 + 4);
-    if (best < 0 || cost <= best) {
-      best = cost;
-      rows = r;
-    }
-  }
-  const int nby = (L.ny + rows - 1) / rows;
-  const dim3 grid((unsigned)nbx * nby), block(nt);
+static void pair_launch(const S* A, S* B, const Layout& L, const DdfParams& prm, const PairShape& p,
+                        hipStream_t s) {
+  const dim3 grid((unsigned)p.nbx * p.parts), block(p.threads);
   if (prm.eos)
-    k_ddf_pair<S, WALLS, 2><<<grid, block, 0, s>>>(A, B, L.nx, L.ny, L.pitch, L.plane, prm, rows, nbx);
+    k_ddf_pair<S, WALLS, 2><<<grid, block, 0, s>>>(A, B, L.nx, L.ny, L.pitch, L.plane, prm, p.rows, p.nbx);
   else if (prm.ext())
-    k_ddf_pair<S, WALLS, 1><<<grid, block, 0, s>>>(A, B, L.nx, L.ny, L.pitch, L.plane, prm, rows, nbx);
+    k_ddf_pair<S, WALLS, 1><<<grid, block, 0, s>>>(A, B, L.nx, L.ny, L.pitch, L.plane, prm, p.rows, p.nbx);
   else
-    k_ddf_pair<S, WALLS, 0><<<grid, block, 0, s>>>(A, B, L.nx, L.ny, L.pitch, L.plane, prm, rows, nbx);
+    k_ddf_pair<S, WALLS, 0><<<grid, block, 0, s>>>(A, B, L.nx, L.ny, L.pitch, L.plane, prm, p.rows, p.nbx);
 }
 
 hipError_t launch_ddf_pair(int fmt, bool walls, const void* A, void* B, const Layout& L,
-                           const DdfParams& prm, hipStream_t s) {
+                           const DdfParams& prm, const PairShape& shape, hipStream_t s) {
   if (fmt != 0 || prm.phi == 2) return hipErrorInvalidValue;
   if (prm.neq && (!walls || L.ny < 3 || prm.src)) return hipErrorInvalidValue;
   const float* a = static_cast<const float*>(A);
   float* b = static_cast<float*>(B);
-  if (prm.neq) pair_launch<float, 2>(a, b, L, prm, s);
-  else if (walls) pair_launch<float, 1>(a, b, L, prm, s);
-  else pair_launch<float, 0>(a, b, L, prm, s);
+  if (prm.neq) pair_launch<float, 2>(a, b, L, prm, shape, s);
+  else if (walls) pair_launch<float, 1>(a, b, L, prm, shape, s);
+  else pair_launch<float, 0>(a, b, L, prm, shape, s);
   return hipGetLastError();
 }
 

@@ -13,6 +13,7 @@
 #include "host_copy.h"
 #include "lbm.h"
 #include "lbm_internal.h"
+#include "routes.h"
 
 using namespace lbm;
 
@@ -33,6 +34,8 @@ struct lbm_ctx {
   int planes = 9;    // stored population planes per buffer
   bool pair3 = false;  // isothermal D3Q27: two steps per launch (while no force is set)
   bool multi = false;  // several steps per launch, from one buffer into the other
+  bool pair = false;   // double distribution, D2Q9: two steps per launch (with the present sources)
+  PairShape pair_shape;
   bool aa = false;   // one buffer, in place (isothermal model): layout alternates with t parity
   DdfParams dp{};
   double* fld = nullptr;  // D3Q27 double distribution: derivative fields
@@ -96,13 +99,19 @@ int hip_fail(lbm_ctx* c, hipError_t e, const char* where) {
     if (e_ != hipSuccess) return hip_fail((ctx), e_, #expr); \
   } while (0)
 
-// The double-distribution kernels take the sources of the next collision from DdfParams.
+// The double-distribution kernels take the sources of the next collision from DdfParams, which also
+// decide between their launches.
 void sync_sources(lbm_ctx* c) {
   c->dp.Fx = c->F.x;
   c->dp.Fy = c->F.y;
   c->dp.Fz = c->F.z;
   c->dp.Q = c->heat;
-  c->dp.src = c->F.on() || c->heat != 0.0;
+  const bool src = c->F.on() || c->heat != 0.0;
+  const bool same = c->pair_shape.rows > 0 && src == c->dp.src;
+  c->dp.src = src;
+  if (!c->ddf || c->D != 2 || same) return;
+  c->pair_shape = ddf_pair_shape(c->L, c->dp);
+  c->pair = ddf_pair_supported(c->fmt, c->L, c->dp, c->pair_shape);
 }
 
 struct Plan {
@@ -319,7 +328,7 @@ bool plan_aligned(const Plan& P) {
 int batch_steps(const lbm_ctx* c) {
   if (c->multi) return c->aa && (c->t & 1) ? 0 : kMultiSteps;
   if (c->pair3) return c->F.on() ? 0 : 2;
-  return c->ddf && c->D == 2 && ddf_pair_supported(c->fmt, c->L, c->dp) ? 2 : 0;
+  return c->pair ? 2 : 0;
 }
 
 // Launches of up to `most` steps each that take an even number of the next `ahead` steps. keep: the
@@ -604,7 +613,7 @@ int lbm_step(lbm_ctx* c, int64_t n) {
         else if (c->pair3)
           e = launch_bgk_d3q27_pair(c->A, c->B, c->L, c->omega, c->stream);
         else
-          e = launch_ddf_pair(c->fmt, c->p.wall_y != 0, c->A, c->B, c->L, c->dp, c->stream);
+          e = launch_ddf_pair(c->fmt, c->p.wall_y != 0, c->A, c->B, c->L, c->dp, c->pair_shape, c->stream);
         if (e != hipSuccess) {
           state_home(c);
           return hip_fail(c, e, "step kernel launch");

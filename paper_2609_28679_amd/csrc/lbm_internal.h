@@ -31,6 +31,15 @@ struct Grid {
   int blocks() const { return nbx * nby; }
 };
 
+// Launch shape of two double-distribution D2Q9 steps (routes.h).
+struct PairShape {
+  int threads = 0;     // per workgroup
+  int nbx = 0, parts = 0;  // workgroups along x and y
+  int rows = 0;        // rows of a workgroup
+  int rounds = 0;      // of workgroups over the chip
+  int64_t turns = -1;  // rows that the chip walks one after the other
+};
+
 // Uniform body force per unit volume (lattice units); zero when the context has none.
 struct Force {
   double x = 0.0, y = 0.0, z = 0.0;
@@ -130,7 +139,6 @@ hipError_t launch_decode_f(int kind, int D, int i, const void* A, const Layout& 
 // Double-distribution kernels (D2Q9). Storage format fmt / kind: 0 float32, 1 float64 (planes
 // 0..8 hold f - w, 9..17 hold g - v); 2 bfloat16, 3 float16 reduced storage (4 float32 moment
 // planes, then 6 f and 8 g uint16 planes).
-Grid make_grid_ddf(const Layout& L, int halo, bool reduced);
 // out[0..8] = f^eq, out[9..17] = g^eq at rho = 1, u = 0, T = 1 (18 doubles, device memory).
 hipError_t launch_ddf_rest_state(const DdfParams& prm, double* out, hipStream_t s);
 // nb: boundary-row buffer of the non-equilibrium extrapolation walls (2 x 18 rows of `pitch`
@@ -141,13 +149,10 @@ hipError_t launch_ddf_rest_state(const DdfParams& prm, double* out, hipStream_t 
 hipError_t launch_ddf(int fmt, bool walls, bool pull, const void* A, void* B, const Layout& L,
                       const Grid& G, const DdfParams& prm, float s_enc, float s_dec,
                       double* partials, void* nb, int* records, hipStream_t s);
-// Most diagnostics records any step of the format writes (grid G of the plan).
-int ddf_max_records(const Layout& L, const Grid& G, int phi, int fmt);
-// Two steps in one launch, from A to B (float32 / float64 storage, phi 0 or 1); NEQ walls rebuild
-// their rows inside.
-bool ddf_pair_supported(int fmt, const Layout& L, const DdfParams& prm);
+// Two steps in one launch, from A to B (float32 storage, phi 0 or 1); NEQ walls rebuild their rows
+// inside. The shape is the one of these parameters (ddf_pair_shape).
 hipError_t launch_ddf_pair(int fmt, bool walls, const void* A, void* B, const Layout& L,
-                           const DdfParams& prm, hipStream_t s);
+                           const DdfParams& prm, const PairShape& shape, hipStream_t s);
 hipError_t launch_init_ddf(int kind, const double* rho, const double* u, const double* T,
                            void* A, const Layout& L, const DdfParams& prm, hipStream_t s);
 hipError_t launch_moments_ddf(int kind, const void* A, const Layout& L, const DdfParams& prm,

@@ -1,0 +1,148 @@
+// Host rules of the kernels that come in several shapes: which launches a lattice takes and how they
+// are cut into workgroups. No device code.
+#pragma once
+
+#include <algorithm>
+#include <climits>
+#include <cstdlib>
+
+#include "lbm_internal.h"
+
+namespace lbm {
+
+constexpr int kCus = 256;  // compute units
+
+inline int64_t div_up(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// ---- double distribution, D2Q9: one step per launch ----------------------------------------------
+// Columns owned by a workgroup: its threads less the halo and, when the rows are staged (the kernel's
+// TXI), one staging-only thread per side.
+inline Grid make_grid_ddf(const Layout& L, int halo, bool reduced) {
+  Grid G;
+  G.bx = kBlock;
+  const int txi = kBlock - 2 * halo - (reduced ? 2 : 0);
+  G.nbx = (L.nx + txi - 1) / txi;
+  // rows per workgroup from sweeps on MI355X at 4096^2 with walls (float32, central Phi:
+  // 2 -> 588 us, 4 -> 553, 8 -> 580, 16 -> 599; float32, upwind Phi: 4 -> 646, 8 -> 596,
+  // 16 -> 586; reduced bf16: 8 -> 676, 16 -> 602, 32 -> 604): short windows give more
+  // workgroups in flight, taller ones amortise the halo rows (two per side for the upwind
+  // stencil) and the staged kernel's 2-row staging halo
+  G.rows = reduced ? 16 : (halo == 2 ? 16 : 4);
+#ifdef LBM_TUNING_ENV
+  if (const char* v = getenv("LBM_DDF_ROWS")) G.rows = atoi(v);
+#endif
+  fit_rows(G, L.ny);
+  return G;
+}
+
+// Rows per workgroup of the extended collisions (sources, transport control, van der Waals):
+// their longer per-row arithmetic favours taller windows than the plain step's. Measured at
+// 4096^2 with walls, central Phi, float32 (4 / 6 / 8 / 10 rows): sources 618 / 589 / 582 /
+// 583 us, Pr 0.71 646 / 613 / 601 / 599, van der Waals 719 / 673 / 649 / 644; the plain and NEQ
+// steps keep their 4 (552 / 568 at 6 and 561 / 580).
+constexpr int kDdfExtRows = 8;
+
+// Window rows that the chip walks one after the other: rounds of resident workgroups x (rows + 2
+// halo + 1 for the start). Three workgroups fit a compute unit for the plain float32 step with
+// central Phi, two otherwise.
+inline int64_t ddf_turns(int64_t blocks, int rows, int halo, int per_cu) {
+  return div_up(blocks, (int64_t)kCus * per_cu) * (rows + 2 * halo + 1);
+}
+
+// Lattices that do not fill the chip several times over get lower windows: the rows in
+// [1, G.rows] with the least turns. us per step, the fixed rows -> these: 64^2 plain 9.6 -> 5.9,
+// upwind 28.1 -> 7.9, float16 44.6 -> 11.5, Pr 0.71 with NEQ walls 21.9 -> 10.5; 512^2 plain 16.0 ->
+// 13.8, upwind 38.5 -> 22; 1021 x 509 Pr 0.71 with NEQ walls 38.3 -> 30.6, float16 48.7 -> 32. Of 28
+// sizes from 40 x 20 to 2048^2 in 18 configurations these rows are within 4% of the best ones on
+// average (512^2 with a force 4 rows 17.9, 2 rows 18.2). They are not the best for each: upwind Phi
+// with a van der Waals fluid runs 270 x 2000 5% faster on the fixed 16 rows.
+inline Grid ddf_fill(Grid G, const Layout& L, int halo, int per_cu) {
+  int64_t best = -1;
+  int rows = G.rows;
+  for (int r = 1; r <= G.rows; ++r) {
+    const int64_t cost = ddf_turns(G.nbx * div_up(L.ny, r), r, halo, per_cu);
+    if (best < 0 || cost <= best) {
+      best = cost;
+      rows = r;
+    }
+  }
+  G.rows = rows;
+  fit_rows(G, L.ny);
+  return G;
+}
+
+// Launch grid of one step, from the plan's grid: taller windows for the extended collisions. A step
+// that writes its diagnostics records keeps the plan's windows where the lower ones would write
+// more than there is room for.
+inline Grid ddf_step_grid(Grid G, const Layout& L, int phi, int fmt, bool extended, int room) {
+  if (fmt < 2 && extended && G.rows < kDdfExtRows) {
+    G.rows = kDdfExtRows;
+    fit_rows(G, L.ny);
+  }
+  const int halo = phi == 2 ? 2 : 1;
+  const Grid filled = ddf_fill(G, L, halo, fmt == 0 && halo == 1 && !extended ? 3 : 2);
+  return filled.blocks() <= room ? filled : G;
+}
+
+// Most diagnostics records any step of the format writes (grid G of the plan).
+inline int ddf_max_records(const Layout& L, const Grid& G, int phi, int fmt) {
+  return std::max(ddf_step_grid(G, L, phi, fmt, false, INT_MAX).blocks(),
+                  ddf_step_grid(G, L, phi, fmt, true, INT_MAX).blocks());
+}
+
+// ---- double distribution, D2Q9: two steps per launch ----------------------------------------------
+constexpr int kPairHalo = 3;  // columns per side that only supply neighbours
+
+// Shape of k_ddf_pair: the rows per workgroup that the chip walks in the least turns, one workgroup
+// per compute unit (two for the plain collision without NEQ walls) x (rows + 8 of both steps' halo
+// + 4 for the start).
+inline PairShape ddf_pair_shape(const Layout& L, const DdfParams& prm) {
+  PairShape s;
+  s.threads = std::min(kBlock, (L.nx + 2 * kPairHalo + 63) / 64 * 64);
+  s.nbx = (int)div_up(L.nx, s.threads - 2 * kPairHalo);
+  const int64_t slots = kCus * (int64_t)(prm.ext() || prm.eos || prm.neq ? 1 : 2) * kBlock / s.threads;
+  const int max_rows = std::min(L.ny, 512);
+  for (int r = 1; r <= max_rows; ++r) {
+    const int64_t cost = div_up(s.nbx * div_up(L.ny, r), slots) * (r + 8 + 4);
+    if (s.turns < 0 || cost <= s.turns) {
+      s.turns = cost;
+      s.rows = r;
+    }
+  }
+  s.parts = (int)div_up(L.ny, s.rows);
+  s.rounds = (int)div_up((int64_t)s.nbx * s.parts, slots);
+  return s;
+}
+
+// Where two steps per launch are taken, float32 with central Phi or none. A window row costs more
+// serial time here than in the one-step kernel, and a workgroup walks 12 rows besides its own; what
+// is gained is the memory traffic of large lattices, half of it. us per step, one step / two:
+//   - from 700 000 nodes on, NEQ walls 400 000 (512^2 plain 13.8 / 19.4, 1021 x 509 24.3 / 25.1, 1024^2
+//     46.0 / 35.6, with NEQ walls 512^2 23.3 / 23.9 and 700 x 600 24.4 / 20.0);
+//   - six rows per workgroup or more (240000 x 3 plain 30.5 / 35.6, force 31.6 / 59; 120000 x 6 plain
+//     29.1 / 25.8);
+//   - full workgroups, or for the plain collision those of 64 and 128 threads: the LDS of a workgroup
+//     does not shrink with its threads (10 x 70000 plain 322 / 167, force 351 / 384; 130 x 6000 plain
+//     40.3 / 41.7, with NEQ walls 42.8 / 59.1);
+//   - collisions with a force or heat source, transport control or a van der Waals fluid, which run
+//     one workgroup per compute unit: turns up to 2.46 x those of the one-step launch, with NEQ walls,
+//     whose rows that launch takes from one of their own, 3 x, and where fewer than 63% of the threads
+//     own a column 1.9 x (turns, times: 1000 x 768 with a force 2.67, 31.2 / 31.1, van der Waals 34.2 /
+//     36.3; 900^2 2.45, 37.4 / 36.3 and 41.3 / 41.3; 1024^2 1.83, 51.3 / 44.5 and 58.7 / 51.2; 1021 x
+//     509 Pr 0.71 with NEQ walls 2.75, 29.5 / 28.5; 270 x 2000 the same 2.55, 33.8 / 36.7; 304 x 10605
+//     1.58, 9% faster); with NEQ walls also one round or 16 rows (200000 x 12 van der Waals 134 / 150).
+// Of 80 sizes in 7 collisions no pair of steps is slower than two launches by more than 2.5% under
+// these rules, and none that is left out would gain more than 5%.
+inline bool ddf_pair_supported(int fmt, const Layout& L, const DdfParams& prm, const PairShape& s) {
+  if (fmt != 0 || prm.phi == 2 || L.nx > 1 << 24 || L.nodes() < (prm.neq ? 400000 : 700000)) return false;
+  const bool ext = prm.ext() || prm.eos;
+  if (s.threads < kBlock) return !ext && s.threads != 192;
+  if (s.rows < 6) return false;
+  if (!ext) return true;
+  const bool sparse = (int64_t)L.nx * 100 < (int64_t)s.nbx * s.threads * 63;
+  if (prm.neq && s.rounds > 1 && s.rows < 16) return false;
+  const Grid one = ddf_step_grid(make_grid_ddf(L, 1, false), L, prm.phi, 0, true, INT_MAX);
+  return s.turns * 100 <= ddf_turns(one.blocks(), one.rows, 1, 2) * (sparse ? 190 : (prm.neq ? 300 : 246));
+}
+
+}  // namespace lbm

@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "lbm_internal.h"
+#include "routes.h"
 
 namespace {
 using Op = std::function<void()>;
@@ -103,6 +104,22 @@ void fake_replay(void* s) {
   for (const Op& op : q.graph) q.ops.push_back(op);
 }
 
+// the library's rules for the double distribution (D2Q9)
+int fake_ddf_records(int nx, int ny, int phi, int fmt) {
+  const lbm::Layout L = lbm::make_layout(nx, ny, 1, 4);
+  return lbm::ddf_max_records(L, lbm::make_grid_ddf(L, phi == 2 ? 2 : 1, fmt >= 2), phi, fmt);
+}
+int fake_ddf_pair(int nx, int ny, int src, int full, int eos, int neq) {
+  const lbm::Layout L = lbm::make_layout(nx, ny, 1, 4);
+  lbm::DdfParams prm{};
+  prm.phi = 1;
+  prm.src = src;
+  prm.full = full || eos;
+  prm.eos = eos;
+  prm.neq = neq;
+  return lbm::ddf_pair_supported(0, L, prm, lbm::ddf_pair_shape(L, prm));
+}
+
 // ---- HIP ------------------------------------------------------------------------------------
 hipError_t hipMalloc(void** p, size_t n) {
   Lock lock(mu);
@@ -134,7 +151,7 @@ hipError_t hipHostFree(void* p) {
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t st) {
   Lock lock(mu);
   ++copies;
-  put(st, [=] { std::memcpy(d, s, n); });
+  (void)put(st, [=] { std::memcpy(d, s, n); });
   const void* host = k == hipMemcpyHostToDevice ? s : d;
   Queue& q = queue(st);
   if (k != hipMemcpyDeviceToDevice && !is_pinned(host) && !q.capturing) run(q, q.ops.size());
@@ -217,14 +234,11 @@ Layout make_layout(int nx, int ny, int nz, int) {
 }
 static Grid grid() { return Grid{256, 4, 4, 8}; }
 Grid make_grid(const Layout&) { return grid(); }
-Grid make_grid_ddf(const Layout&, int, bool) { return grid(); }
 Grid make_grid_ddf3(const Layout&) { return grid(); }
 Grid make_grid_red(const Layout&) { return grid(); }
 Grid make_grid_mlp(const Layout&) { return grid(); }
 size_t red_state_bytes(const Layout& L) { return (size_t)L.plane * 24; }
-int ddf_max_records(const Layout&, const Grid&, int, int) { return 2000; }
 int64_t ddf3_max_records(const Layout&, const Grid&) { return 32; }
-bool ddf_pair_supported(int fmt, const Layout&, const DdfParams& prm) { return fmt == 0 && prm.phi != 2; }
 int mlp_partial_count(int B) { return (B + 63) / 64; }
 
 static hipError_t take(const void* A, void* B, int steps, hipStream_t s) {
@@ -247,7 +261,7 @@ hipError_t launch_ddf3(int, bool, bool pull, const void* A, void* B, const Layou
   if (records) *records = 32;
   return pull ? take(A, B, 1, s) : put(s, [=] { count(B) = count(A); });
 }
-hipError_t launch_ddf_pair(int, bool, const void* A, void* B, const Layout&, const DdfParams&, hipStream_t s) { return take(A, B, 2, s); }
+hipError_t launch_ddf_pair(int, bool, const void* A, void* B, const Layout&, const DdfParams&, const PairShape&, hipStream_t s) { return take(A, B, 2, s); }
 
 static hipError_t init(const double* rho, void* A, const Layout& L, hipStream_t s) {
   const size_t n = (size_t)L.nodes();
@@ -278,11 +292,11 @@ hipError_t launch_moments_bgk(int, int D, const void* A, const Layout& L, int, b
 }
 hipError_t launch_moments_bgk_red(const void* A, const Layout& L, double* rho, double* u, hipStream_t s) { return launch_moments_bgk(0, 2, A, L, 0, false, Force{}, rho, u, s); }
 hipError_t launch_moments_ddf(int, const void* A, const Layout& L, const DdfParams&, double* rho, double* u, double* T, double*, hipStream_t s) {
-  fill(A, T, (size_t)L.nodes(), 0.0, s);
+  (void)fill(A, T, (size_t)L.nodes(), 0.0, s);
   return launch_moments_bgk(0, 2, A, L, 0, false, Force{}, rho, u, s);
 }
 hipError_t launch_moments_ddf3(int, const void* A, const Layout& L, const DdfParams&, double* rho, double* u, double* T, double*, hipStream_t s) {
-  fill(A, T, (size_t)L.nodes(), 0.0, s);
+  (void)fill(A, T, (size_t)L.nodes(), 0.0, s);
   return launch_moments_bgk(0, 3, A, L, 0, false, Force{}, rho, u, s);
 }
 hipError_t launch_decode_f(int, int, int i, const void* A, const Layout& L, int, bool, double* f, hipStream_t s) { return fill(A, f, (size_t)L.nodes(), 1000.0 * i, s); }

@@ -32,7 +32,7 @@ def _same(pair, single):
 
 @pytest.mark.parametrize("option", sorted(OPTIONS))
 @pytest.mark.parametrize("density", ["pressure", "literal"])
-@pytest.mark.parametrize("nx,ny", [(250, 2801), (1100, 701)])
+@pytest.mark.parametrize("nx,ny", [(250, 2801), (499, 2003), (1100, 701)])
 def test_walls_equal_single_steps(option, density, nx, ny):
     kw, wall_T, T0 = OPTIONS[option]
     walls = dict(u=((-0.05, 0.0), (0.05, 0.0)), T=wall_T, density=density)
@@ -46,9 +46,25 @@ def test_walls_equal_single_steps(option, density, nx, ny):
     single.close()
 
 
+@pytest.mark.parametrize("option", ["sources", "transport", "vdw"])
+@pytest.mark.parametrize("walls", [False, True])
+@pytest.mark.parametrize("nx,ny", [(1100, 1001), (200, 6001), (30001, 48)])
+def test_extended_collisions_equal_single_steps(option, walls, nx, ny):
+    """Lattices on which these collisions take two steps per launch."""
+    kw, _, T0 = OPTIONS.get(option, (dict(force=(1e-5, 2e-6), heat_source=1e-6), None, 0.9))
+    pair, single = (_lattice(nx, ny, T0, wall_y=walls, **kw) for _ in range(2))
+    for n in (4, 3):
+        pair.step(n)
+        for _ in range(n):
+            single.step(1)
+        _same(pair, single)
+    pair.close()
+    single.close()
+
+
 @pytest.mark.parametrize("walls", [False, True])
 def test_sources_that_change_between_calls(walls):
-    pair, single = (_lattice(1100, 701, 0.9, wall_y=walls, diag_every=9) for _ in range(2))
+    pair, single = (_lattice(1100, 1001, 0.9, wall_y=walls, diag_every=9) for _ in range(2))
     for n, force, heat in ((4, (1e-5, 2e-6), 0.0), (5, (1e-5, 2e-6), 1e-6), (6, (0.0, 0.0), 1e-6),
                            (4, (0.0, 0.0), 0.0), (1, (0.0, 1e-5), 0.0), (2, (0.0, 0.0), 0.0)):
         for lat in (pair, single):

@@ -206,21 +206,23 @@ def test_workspace_without_room_for_several_steps_per_launch(fake, storage, elem
 
 
 def test_workspace_with_records_of_the_plans_windows(fake):
-    """2000 records for the lower windows of this fake's lattices, 1024 for the plan's own."""
-    shape = (40, 65)
+    """Lower windows than the plan's own may write more records."""
+    shape = (3200, 16)
+    records = fake.fake_ddf_records(shape[1], shape[0], 1, 0)
+    assert records > 1024
     full = _workspace_size(fake, shape, model=1)
-    least = full - (_up(2000 * 40) - _up(1024 * 40))
+    least = full - (_up(records * 40) - _up(1024 * 40))
     buf = ctypes.create_string_buffer(full + 256)
     base = (ctypes.addressof(buf) + 255) // 256 * 256
-    for size, room in ((full, 2000), (least, 1024)):
-        c = Context(fake, shape, model=1, phi=2, diag_every=1, workspace=base, workspace_bytes=size)
+    for size, room in ((full, records), (least, 1024)):
+        c = Context(fake, shape, model=1, diag_every=1, workspace=base, workspace_bytes=size)
         c.step(5)
         assert fake.fake_record_room() == room and c.moments() == 5
         c.close()
 
 
 MODELS = {"d2q9": ((40, 65), {}), "d2q9_two": ((40, 65), dict(streaming=1)),
-          "d3q27_two": ((6, 10, 20), dict(streaming=1)), "ddf": ((40, 65), dict(model=1)),
+          "d3q27_two": ((6, 10, 20), dict(streaming=1)), "ddf": ((840, 840), dict(model=1)),
           "bf16": ((40, 65), dict(storage=1))}
 
 
@@ -272,3 +274,35 @@ def test_failing_launch_leaves_a_state_that_can_be_read(fake, model, k):
     c.step(7)
     assert c.moments() == t.value + 7
     c.close()
+
+
+# (nx, ny): us per step of one step per launch / of two, measured on MI355X
+PLAIN, SOURCES, TRANSPORT, VDW = (0, 0, 0, 0), (1, 0, 0, 0), (0, 1, 0, 0), (0, 0, 1, 0)
+NEQ, NEQ_TRANSPORT, NEQ_VDW = (0, 0, 0, 1), (0, 1, 0, 1), (0, 0, 1, 1)
+FASTER = {
+    PLAIN: [(2048, 2048), (1024, 1024), (120000, 6), (250, 3000), (3, 240000), (60, 12000)],
+    SOURCES: [(2048, 2048), (1100, 1001), (900, 900), (30000, 48), (200, 6000)],
+    TRANSPORT: [(2048, 2048), (1024, 1024), (900, 900), (30000, 48), (1100, 1001)],
+    VDW: [(2048, 2048), (1024, 1024), (1100, 1001), (30000, 48)],
+    NEQ: [(2048, 2048), (1021, 509), (700, 600), (120000, 6), (270, 2000), (3, 240000)],
+    NEQ_TRANSPORT: [(2048, 2048), (1021, 509), (700, 640), (304, 10605), (60000, 12), (499, 2003)],
+    NEQ_VDW: [(2048, 2048), (1021, 509), (1000, 768), (60000, 12)],
+}
+SLOWER = {
+    PLAIN: [(512, 512), (240000, 3), (130, 6000)],                           # 1.17, 1.04 x
+    SOURCES: [(240000, 3), (120000, 6), (30, 25000), (130, 6000), (256, 3000), (200000, 12),
+              (768, 1000)],                                                  # 1.87 ... 1.05 x
+    TRANSPORT: [(240000, 3), (120000, 6), (3, 240000), (60, 12000), (130, 6000), (200000, 12)],
+    VDW: [(240000, 3), (3, 240000), (30, 25000), (1024, 700), (1000, 768), (768, 1000), (260, 2900)],
+    NEQ: [(512, 512), (240000, 3), (130, 6000)],                             # 1.20, 1.38 x
+    NEQ_TRANSPORT: [(240000, 3), (3, 240000), (130, 6000), (270, 2000), (311, 1992)],  # 1.33 ... 1.09 x
+    NEQ_VDW: [(240000, 3), (120000, 6), (30, 25000), (200000, 12), (270, 2000)],
+}
+
+
+@pytest.mark.parametrize("options", sorted(FASTER))
+def test_two_ddf_steps_per_launch_where_they_are_faster(fake, options):
+    for nx, ny in FASTER[options]:
+        assert fake.fake_ddf_pair(nx, ny, *options) == 1, (nx, ny)
+    for nx, ny in SLOWER[options]:
+        assert fake.fake_ddf_pair(nx, ny, *options) == 0, (nx, ny)
