@@ -43,17 +43,21 @@ inline Grid make_grid_ddf(const Layout& L, int halo, bool reduced) {
 constexpr int kDdfExtRows = 8;
 
 // Window rows that the chip walks one after the other: rounds of resident workgroups x (rows + 2
-// halo + 1 for the start). Three workgroups fit a compute unit for the plain float32 step with
-// central Phi, two otherwise.
+// halo + 1 for the start), in tenths. Two workgroups share a compute unit, three of the plain
+// float32 step with central Phi; each of the three beyond the first costs a fifth where all
+// workgroups are resident at once (700 x 640: 4 rows, two workgroups per unit, 19.3 us; 3 rows,
+// three per unit, 21.5).
 inline int64_t ddf_turns(int64_t blocks, int rows, int halo, int per_cu) {
-  return div_up(blocks, (int64_t)kCus * per_cu) * (rows + 2 * halo + 1);
+  int64_t rounds = 10 * div_up(blocks, (int64_t)kCus * per_cu);
+  if (per_cu == 3 && rounds == 10) rounds += 2 * (div_up(blocks, kCus) - 1);
+  return rounds * (rows + 2 * halo + 1);
 }
 
 // Lattices that do not fill the chip several times over get lower windows: the rows in
 // [1, G.rows] with the least turns. us per step, the fixed rows -> these: 64^2 plain 9.6 -> 5.9,
 // upwind 28.1 -> 7.9, float16 44.6 -> 11.5, Pr 0.71 with NEQ walls 21.9 -> 10.5; 512^2 plain 16.0 ->
 // 13.8, upwind 38.5 -> 22; 1021 x 509 Pr 0.71 with NEQ walls 38.3 -> 30.6, float16 48.7 -> 32. Of 28
-// sizes from 40 x 20 to 2048^2 in 18 configurations these rows are within 4% of the best ones on
+// sizes from 40 x 20 to 2048^2 in 18 configurations these rows are within 3% of the best ones on
 // average (512^2 with a force 4 rows 17.9, 2 rows 18.2). They are not the best for each: upwind Phi
 // with a van der Waals fluid runs 270 x 2000 5% faster on the fixed 16 rows.
 inline Grid ddf_fill(Grid G, const Layout& L, int halo, int per_cu) {
@@ -142,7 +146,8 @@ inline bool ddf_pair_supported(int fmt, const Layout& L, const DdfParams& prm, c
   const bool sparse = (int64_t)L.nx * 100 < (int64_t)s.nbx * s.threads * 63;
   if (prm.neq && s.rounds > 1 && s.rows < 16) return false;
   const Grid one = ddf_step_grid(make_grid_ddf(L, 1, false), L, prm.phi, 0, true, INT_MAX);
-  return s.turns * 100 <= ddf_turns(one.blocks(), one.rows, 1, 2) * (sparse ? 190 : (prm.neq ? 300 : 246));
+  // one-step turns in tenths
+  return s.turns * 1000 <= ddf_turns(one.blocks(), one.rows, 1, 2) * (sparse ? 190 : (prm.neq ? 300 : 246));
 }
 
 }  // namespace lbm

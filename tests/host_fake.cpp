@@ -109,6 +109,10 @@ int fake_ddf_records(int nx, int ny, int phi, int fmt) {
   const lbm::Layout L = lbm::make_layout(nx, ny, 1, 4);
   return lbm::ddf_max_records(L, lbm::make_grid_ddf(L, phi == 2 ? 2 : 1, fmt >= 2), phi, fmt);
 }
+int fake_ddf_rows(int nx, int ny, int phi, int fmt, int ext) {
+  const lbm::Layout L = lbm::make_layout(nx, ny, 1, 4);
+  return lbm::ddf_step_grid(lbm::make_grid_ddf(L, phi == 2 ? 2 : 1, fmt >= 2), L, phi, fmt, ext, 1 << 30).rows;
+}
 int fake_ddf_pair(int nx, int ny, int src, int full, int eos, int neq) {
   const lbm::Layout L = lbm::make_layout(nx, ny, 1, 4);
   lbm::DdfParams prm{};

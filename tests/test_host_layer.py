@@ -306,3 +306,16 @@ def test_two_ddf_steps_per_launch_where_they_are_faster(fake, options):
         assert fake.fake_ddf_pair(nx, ny, *options) == 1, (nx, ny)
     for nx, ny in SLOWER[options]:
         assert fake.fake_ddf_pair(nx, ny, *options) == 0, (nx, ny)
+
+
+@pytest.mark.parametrize("nx,ny,phi,fmt,ext,rows", [
+    (700, 640, 1, 0, 0, 4),   # 19.3 us a step; 3 rows 21.8
+    (512, 512, 1, 0, 0, 2),   # 14.0; 4 rows 16.0
+    (640, 500, 1, 0, 0, 2),   # 15.4; 4 rows 18.0
+    (2048, 2048, 1, 0, 0, 4),
+    (512, 512, 1, 0, 1, 4),   # 17.9; 8 rows 22.7
+    (1021, 509, 1, 0, 1, 5),  # 24.8; 8 rows 32.1
+    (64, 64, 2, 0, 0, 1),
+])
+def test_window_rows_of_one_ddf_step(fake, nx, ny, phi, fmt, ext, rows):
+    assert fake.fake_ddf_rows(nx, ny, phi, fmt, ext) == rows
