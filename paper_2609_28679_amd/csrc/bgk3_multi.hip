@@ -14,15 +14,11 @@
 // and 580 at 7 rows), so those runs keep one step per launch; lattices of one in-place buffer do
 // too (100^3: 41 us either way).
 #include "bgk_common.h"
-
-#include <algorithm>
+#include "routes.h"
 
 namespace lbm {
 
-constexpr int kP3Rows = 11;                    // region rows: owned rows and one more on either side
-constexpr int kP3Own = kP3Rows - 2;
 constexpr int kP3Threads = 64 * (kP3Rows + 1);  // a wavefront per row, one for the halo columns
-constexpr int kP3Cus = 256;
 
 __global__ void __launch_bounds__(kP3Threads)
 k_bgk_d3q27_pair(const float* __restrict__ A, float* __restrict__ B, int nx, int ny, int nz,
@@ -120,24 +116,11 @@ k_bgk_d3q27_pair(const float* __restrict__ A, float* __restrict__ B, int nx, int
   }
 }
 
-hipError_t launch_bgk_d3q27_pair(const void* A, void* B, const Layout& L, double omega,
-                                 hipStream_t s) {
-  const int nbx = (L.nx + 63) / 64, nby = (L.ny + kP3Own - 1) / kP3Own;
-  const int64_t T = (int64_t)nbx * nby;
-  // ranges of planes: the fewest planes in turn over the rounds of one workgroup per compute unit
-  int nzc = 1;
-  int64_t best = -1;
-  for (int c = 1; c <= std::min(L.nz, 64); ++c) {
-    if (T * c > (int64_t)1 << 21) break;
-    const int64_t cost = (T * c + kP3Cus - 1) / kP3Cus * ((L.nz + c - 1) / c + 3);
-    if (best < 0 || cost < best) {
-      best = cost;
-      nzc = c;
-    }
-  }
-  k_bgk_d3q27_pair<<<(unsigned)(T * nzc), kP3Threads, 0, s>>>(
+hipError_t launch_bgk_d3q27_pair(const void* A, void* B, const Layout& L, const Pair3Shape& p,
+                                 double omega, hipStream_t s) {
+  k_bgk_d3q27_pair<<<(unsigned)((int64_t)p.nbx * p.nby * p.ranges), kP3Threads, 0, s>>>(
       static_cast<const float*>(A), static_cast<float*>(B), L.nx, L.ny, L.nz, L.pitch, L.plane,
-      omega, nbx, nby, nzc);
+      omega, p.nbx, p.nby, p.ranges);
   return hipGetLastError();
 }
 

@@ -36,6 +36,7 @@ struct lbm_ctx {
   bool multi = false;  // several steps per launch, from one buffer into the other
   bool pair = false;   // double distribution, D2Q9: two steps per launch (with the present sources)
   PairShape pair_shape;
+  Pair3Shape pair3_shape;
   bool aa = false;   // one buffer, in place (isothermal model): layout alternates with t parity
   DdfParams dp{};
   double* fld = nullptr;  // D3Q27 double distribution: derivative fields
@@ -535,7 +536,9 @@ int lbm_create(const lbm_params* p, const double* rho0, const double* u0, const 
   c->partial_slots = P.partial_slots;
   c->A = c->ws + P.off_A;
   c->multi = P.multi;
-  c->pair3 = !P.ddf && P.D == 3 && !P.aa && P.kind == 0 && !p->wall_y && p->nx <= 1 << 24;
+  c->pair3_shape = bgk3_pair_shape(c->L);
+  c->pair3 = !P.ddf && P.D == 3 && !P.aa && P.kind == 0 && !p->wall_y &&
+             bgk3_pair_supported(c->L, c->pair3_shape);
   c->B = P.aa ? (P.multi ? c->ws + P.off_read : nullptr) : c->ws + P.off_B;
   c->partials = reinterpret_cast<double*>(c->ws + P.off_part);
   c->history = reinterpret_cast<double*>(c->ws + P.off_hist);
@@ -611,7 +614,7 @@ int lbm_step(lbm_ctx* c, int64_t n) {
         if (c->multi)
           e = launch_bgk_d2q9_multi(c->kind, c->A, c->B, c->L, c->aa, c->omega, c->F, c->p.wall_y != 0, T, c->stream);
         else if (c->pair3)
-          e = launch_bgk_d3q27_pair(c->A, c->B, c->L, c->omega, c->stream);
+          e = launch_bgk_d3q27_pair(c->A, c->B, c->L, c->pair3_shape, c->omega, c->stream);
         else
           e = launch_ddf_pair(c->fmt, c->p.wall_y != 0, c->A, c->B, c->L, c->dp, c->pair_shape, c->stream);
         if (e != hipSuccess) {

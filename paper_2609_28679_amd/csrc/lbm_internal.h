@@ -40,6 +40,11 @@ struct PairShape {
   int64_t turns = -1;  // rows that the chip walks one after the other
 };
 
+// Launch shape of two isothermal D3Q27 steps (routes.h): tiles along x and y, ranges of planes.
+struct Pair3Shape {
+  int nbx = 0, nby = 0, ranges = 1;
+};
+
 // Uniform body force per unit volume (lattice units); zero when the context has none.
 struct Force {
   double x = 0.0, y = 0.0, z = 0.0;
@@ -122,8 +127,8 @@ hipError_t launch_bgk_d2q9_multi(int kind, const void* A, void* B, const Layout&
                                  double omega, const Force& F, bool walls, int steps,
                                  hipStream_t s);
 // Two D3Q27 steps in one launch, from A to B (two buffers, float32, periodic, no force).
-hipError_t launch_bgk_d3q27_pair(const void* A, void* B, const Layout& L, double omega,
-                                 hipStream_t s);
+hipError_t launch_bgk_d3q27_pair(const void* A, void* B, const Layout& L, const Pair3Shape& shape,
+                                 double omega, hipStream_t s);
 // swap: store population i in slot Q-1-i (single-buffer state at an even step count). With a
 // force the equilibrium is collided once (the stored state is post-collision at t = 0).
 hipError_t launch_init_bgk(int kind, int D, const double* rho, const double* u, void* A,

@@ -150,4 +150,38 @@ inline bool ddf_pair_supported(int fmt, const Layout& L, const DdfParams& prm, c
   return s.turns * 1000 <= ddf_turns(one.blocks(), one.rows, 1, 2) * (sparse ? 190 : (prm.neq ? 300 : 246));
 }
 
+// ---- isothermal D3Q27: two steps per launch -------------------------------------------------------
+constexpr int kP3Rows = 11;         // region rows: owned rows and one more on either side
+constexpr int kP3Own = kP3Rows - 2;
+
+// Ranges of planes: the fewest planes in turn over the rounds of one workgroup per compute unit.
+inline Pair3Shape bgk3_pair_shape(const Layout& L) {
+  Pair3Shape s;
+  s.nbx = (int)div_up(L.nx, 64);
+  s.nby = (int)div_up(L.ny, kP3Own);
+  const int64_t tiles = (int64_t)s.nbx * s.nby;
+  int64_t best = -1;
+  for (int c = 1; c <= std::min(L.nz, 64); ++c) {
+    if (tiles * c > (int64_t)1 << 21) break;
+    const int64_t cost = div_up(tiles * c, kCus) * (div_up(L.nz, c) + 3);
+    if (best < 0 || cost < best) {
+      best = cost;
+      s.ranges = c;
+    }
+  }
+  return s;
+}
+
+// Where two steps per launch are taken (two buffers, float32, periodic, no force). A workgroup takes
+// whole tiles of 64 columns, marches over three planes besides its own, and the chip needs one for
+// nearly every compute unit. us per step, one step / two: 64^3 12.5 / 12.1, but 48^3 7.9 / 11.0
+// and 32^3 5.0 / 8.4; 100 x 100 x 20 12.6 / 12.4; 129 x 500 x 20 68 / 60; one plane 2000^2 164 / 209,
+// two 1000 x 500 41.7 / 45.4, three 1000^2 124 / 111; 64 x 9 x 200, 64 workgroups, 7.3 / 14.8 and 128
+// x 9 x 300, 128, 16.1 / 20.2, but 700 x 9 x 64 19.5 / 14.9; 30 x 300 x 64, 47% of the columns, 50 /
+// 32, 3 x 3 x 100000, 5%, 592 / 3545.
+inline bool bgk3_pair_supported(const Layout& L, const Pair3Shape& s) {
+  return L.nx <= 1 << 24 && L.nodes() >= 200000 && L.nz >= 3 &&
+         (int64_t)s.nbx * s.nby * s.ranges >= 192 && 5 * L.nx >= 2 * 64 * s.nbx;
+}
+
 }  // namespace lbm

@@ -113,6 +113,10 @@ int fake_ddf_rows(int nx, int ny, int phi, int fmt, int ext) {
   const lbm::Layout L = lbm::make_layout(nx, ny, 1, 4);
   return lbm::ddf_step_grid(lbm::make_grid_ddf(L, phi == 2 ? 2 : 1, fmt >= 2), L, phi, fmt, ext, 1 << 30).rows;
 }
+int fake_bgk3_pair(int nx, int ny, int nz) {
+  const lbm::Layout L = lbm::make_layout(nx, ny, nz, 4);
+  return lbm::bgk3_pair_supported(L, lbm::bgk3_pair_shape(L));
+}
 int fake_ddf_pair(int nx, int ny, int src, int full, int eos, int neq) {
   const lbm::Layout L = lbm::make_layout(nx, ny, 1, 4);
   lbm::DdfParams prm{};
@@ -253,7 +257,7 @@ hipError_t launch_bgk_d3q27(int, const void* A, void* B, const Layout&, const Gr
 hipError_t launch_bgk_d2q9_aa(int, bool, void* A, const Layout&, const Grid&, double, const Force&, bool, double*, hipStream_t s) { return take(A, A, 1, s); }
 hipError_t launch_bgk_d3q27_aa(int, bool, void* A, const Layout&, const Grid&, double, const Force&, bool, double*, hipStream_t s) { return take(A, A, 1, s); }
 hipError_t launch_bgk_d2q9_multi(int, const void* A, void* B, const Layout&, bool, double, const Force&, bool, int steps, hipStream_t s) { return take(A, B, steps, s); }
-hipError_t launch_bgk_d3q27_pair(const void* A, void* B, const Layout&, double, hipStream_t s) { return take(A, B, 2, s); }
+hipError_t launch_bgk_d3q27_pair(const void* A, void* B, const Layout&, const Pair3Shape&, double, hipStream_t s) { return take(A, B, 2, s); }
 hipError_t launch_bgk_d2q9_red(int, const void* A, void* B, const Layout&, const Grid&, double, bool, float, float, double*, hipStream_t s) { return take(A, B, 1, s); }
 hipError_t launch_bgk_d2q9_mlp(const void* A, void* B, const Layout&, const Grid&, double, bool, const float*, double, unsigned long long*, double*, hipStream_t s) { return take(A, B, 1, s); }
 hipError_t launch_ddf(int, bool, bool pull, const void* A, void* B, const Layout&, const Grid&, const DdfParams&, float, float, double*, void*, int* records, hipStream_t s) {

@@ -7,7 +7,7 @@ pytestmark = pytest.mark.gpu
 CASES = {
     "d2q9": ((300, 130), {}),
     "d2q9_two": ((300, 130), dict(streaming="two", wall_y=True)),
-    "d3q27_two": ((20, 30, 70), dict(lattice="D3Q27", streaming="two")),
+    "d3q27_two": ((20, 100, 100), dict(lattice="D3Q27", streaming="two")),
     "ddf": ((700, 1024), dict(model="ddf", tau=0.6)),
     "ddf_small": ((90, 130), dict(model="ddf", tau=0.6, phi=2)),
 }

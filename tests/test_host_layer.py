@@ -222,7 +222,7 @@ def test_workspace_with_records_of_the_plans_windows(fake):
 
 
 MODELS = {"d2q9": ((40, 65), {}), "d2q9_two": ((40, 65), dict(streaming=1)),
-          "d3q27_two": ((6, 10, 20), dict(streaming=1)), "ddf": ((840, 840), dict(model=1)),
+          "d3q27_two": ((20, 100, 100), dict(streaming=1)), "ddf": ((840, 840), dict(model=1)),
           "bf16": ((40, 65), dict(storage=1))}
 
 
@@ -319,3 +319,13 @@ def test_two_ddf_steps_per_launch_where_they_are_faster(fake, options):
 ])
 def test_window_rows_of_one_ddf_step(fake, nx, ny, phi, fmt, ext, rows):
     assert fake.fake_ddf_rows(nx, ny, phi, fmt, ext) == rows
+
+
+def test_two_d3q27_steps_per_launch_where_they_are_faster(fake):
+    for shape in ((64, 64, 64), (100, 100, 20), (129, 500, 20), (1000, 1000, 3), (700, 9, 64),
+                  (66, 20, 1000), (30, 300, 64), (256, 256, 256)):
+        assert fake.fake_bgk3_pair(*shape) == 1, shape
+    # 1.4 to 2 times slower, and six times on 3 x 3 columns
+    for shape in ((10, 10, 10), (32, 32, 32), (48, 48, 48), (3000, 1, 1), (65, 300, 4),
+                  (2000, 2000, 1), (1000, 500, 2), (64, 9, 200), (128, 9, 300), (3, 3, 100000)):
+        assert fake.fake_bgk3_pair(*shape) == 0, shape
