@@ -54,22 +54,23 @@ inline int64_t ddf_turns(int64_t blocks, int rows, int halo, int per_cu) {
 }
 
 // Lattices that do not fill the chip several times over get lower windows: the rows in
-// [1, G.rows] with the least turns. us per step, the fixed rows -> these: 64^2 plain 9.6 -> 5.9,
+// [1, G.rows] with the least turns, where those are 5% fewer (4096^2 bfloat16 / float16: 14 rows, 1%
+// fewer turns, 527 / 538 us, 16 rows 514 / 521, whose halo rows are fewer). us per step, the fixed rows -> these: 64^2 plain 9.6 -> 5.9,
 // upwind 28.1 -> 7.9, float16 44.6 -> 11.5, Pr 0.71 with NEQ walls 21.9 -> 10.5; 512^2 plain 16.0 ->
 // 13.8, upwind 38.5 -> 22; 1021 x 509 Pr 0.71 with NEQ walls 38.3 -> 30.6, float16 48.7 -> 32. Of 28
 // sizes from 40 x 20 to 2048^2 in 18 configurations these rows are within 3% of the best ones on
 // average (512^2 with a force 4 rows 17.9, 2 rows 18.2). They are not the best for each: upwind Phi
 // with a van der Waals fluid runs 270 x 2000 5% faster on the fixed 16 rows.
 inline Grid ddf_fill(Grid G, const Layout& L, int halo, int per_cu) {
+  auto turns = [&](int r) { return ddf_turns(G.nbx * div_up(L.ny, r), r, halo, per_cu); };
   int64_t best = -1;
   int rows = G.rows;
-  for (int r = 1; r <= G.rows; ++r) {
-    const int64_t cost = ddf_turns(G.nbx * div_up(L.ny, r), r, halo, per_cu);
-    if (best < 0 || cost <= best) {
-      best = cost;
+  for (int r = 1; r <= G.rows; ++r)
+    if (best < 0 || turns(r) <= best) {
+      best = turns(r);
       rows = r;
     }
-  }
+  if (best * 100 > turns(G.rows) * 95) rows = G.rows;
   G.rows = rows;
   fit_rows(G, L.ny);
   return G;
@@ -83,6 +84,9 @@ inline Grid ddf_step_grid(Grid G, const Layout& L, int phi, int fmt, bool extend
     G.rows = kDdfExtRows;
     fit_rows(G, L.ny);
   }
+  // 16-bit storage stages two rows more per window: lower ones pay up to two rounds only (2048^2, three
+  // rounds: 13 rows 146 us, 16 rows 137; 3000^2 15 rows 305, 16 rows 282-295)
+  if (fmt >= 2 && G.blocks() > 2 * 2 * kCus) return G;
   const int halo = phi == 2 ? 2 : 1;
   const Grid filled = ddf_fill(G, L, halo, fmt == 0 && halo == 1 && !extended ? 3 : 2);
   return filled.blocks() <= room ? filled : G;

@@ -313,6 +313,10 @@ def test_two_ddf_steps_per_launch_where_they_are_faster(fake, options):
     (512, 512, 1, 0, 0, 2),   # 14.0; 4 rows 16.0
     (640, 500, 1, 0, 0, 2),   # 15.4; 4 rows 18.0
     (2048, 2048, 1, 0, 0, 4),
+    (4096, 4096, 1, 2, 0, 16),  # bfloat16: 514; 14 rows 527
+    (2048, 2048, 1, 3, 0, 16),  # float16: 137; 13 rows 146
+    (3000, 3000, 1, 2, 0, 16),  # 282; 15 rows 305
+    (512, 512, 1, 3, 0, 4),     # 22.2; 16 rows 40.2
     (512, 512, 1, 0, 1, 4),   # 17.9; 8 rows 22.7
     (1021, 509, 1, 0, 1, 5),  # 24.8; 8 rows 32.1
     (64, 64, 2, 0, 0, 1),
