@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
     (dict(), 64, 64, 728320),
     (dict(wall_y=True), 65, 2000, 14872320),
     (dict(storage="fp64"), 1001, 515, 59049216),
-    (dict(model="ddf", storage="fp16"), 2000, 2051, 534363392),
+    (dict(model="ddf", storage="fp16"), 2000, 2051, 534363392),  # nothing to leave out
     (dict(model="ddf", phi=2), 2000, 2051, 769832192),
 ])
 def test_least_workspace(monkeypatch, kw, nx, ny, least):
@@ -36,7 +36,7 @@ def test_least_workspace(monkeypatch, kw, nx, ny, least):
     monkeypatch.setattr(lib, "lbm_workspace_size", capped)
     small = binding.Lattice(rho, u, T, tau=0.8, diag_every=7, **kw)
     monkeypatch.setattr(lib, "lbm_workspace_size", size_of)
-    assert sizes[0] > least
+    assert sizes[0] >= least
     full.step(23)
     small.step(23)
     for a, b in zip(full.moments(), small.moments()):
