@@ -18,6 +18,11 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
+# Vector instructions per second of the chip: 1024 SIMDs, four cycles each, 2.4 GHz (wavefronts of
+# 64; float64 and float32 issue at the same rate).
+VALU_PEAK = 1024 * 2.4e9 / 4
+# Most time steps per launch of the kernels that take several.
+STEPS_PER_LAUNCH = {"d2q9_bgk": 6, "d2q9_ddf": 2, "d3q27_bgk": 2}
 PROFILE_COUNTERS = os.path.join(ROOT, "profiles", "counters_d2q9_bgk_fp32_2048.txt")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2609_28679_amd", "csrc", f)
                   for f in ("bgk_multi.hip", "bgk_common.h", "device_common.h")]
@@ -42,9 +47,9 @@ def source_digest(paths):
     return h.hexdigest()[:16]
 
 
-def counter_traffic(nodes):
-    """HBM bytes per launch from the committed rocprofv3 counter summary, if it was taken on
-    the current kernel source; None otherwise."""
+def headline_counters(nodes):
+    """The committed rocprofv3 counter summary of the headline kernel if it was taken on the
+    current kernel source and this many nodes; None otherwise."""
     if not os.path.exists(PROFILE_COUNTERS):
         return None
     kv = {}
@@ -56,7 +61,13 @@ def counter_traffic(nodes):
         return None
     if int(kv.get("nodes", -1)) != nodes:
         return None
-    return float(kv["hbm_bytes_per_launch"])
+    return kv
+
+
+def counter_traffic(nodes):
+    """Bytes per launch of six steps from the committed counter summary, or None."""
+    kv = headline_counters(nodes)
+    return float(kv["hbm_bytes_per_launch"]) if kv else None
 
 
 def time_lattice(lat, steps, warmup):
@@ -70,7 +81,9 @@ def time_lattice(lat, steps, warmup):
     return time.perf_counter() - t0, ms
 
 
-def variant(name, make, steps, warmup, bytes_per_node, extra=None):
+def variant(name, make, steps, warmup, bytes_per_node, extra=None, steps_per_launch=1):
+    """bytes_per_node: a state read and written once, which is what a launch has to move; a launch
+    that takes several steps moves it once for all of them."""
     import torch
     lat = make()
     wall, ms = time_lattice(lat, steps, warmup)
@@ -79,12 +92,12 @@ def variant(name, make, steps, warmup, bytes_per_node, extra=None):
     del lat
     torch.cuda.empty_cache()
     per_launch_s = ms / 1e3 / steps
-    gbs = bytes_per_node * nodes / per_launch_s / 1e9
+    gbs = bytes_per_node / steps_per_launch * nodes / per_launch_s / 1e9
     out = {"mlups": round(nodes * steps / wall / 1e6, 1),
            "kernel_us": round(per_launch_s * 1e6, 2),
            "algorithmic_GBs": round(gbs, 1),
            "hbm_frac": round(gbs / HBM_PEAK_GBS, 4),
-           "bytes_per_node": bytes_per_node}
+           "bytes_per_node": bytes_per_node, "steps_per_launch": steps_per_launch}
     if extra:
         out.update(extra)
     log("%s: %s" % (name, out))
@@ -253,14 +266,19 @@ def main():
     torch.cuda.empty_cache()
     mlups = nodes * args.steps / wall / 1e6
     per_launch_s = ms / 1e3 / args.steps
-    bytes_per_node = 72
+    # a state read and written once per launch of six steps
+    bytes_per_node = 72 / STEPS_PER_LAUNCH["d2q9_bgk"]
     achieved = bytes_per_node * nodes / per_launch_s / 1e9
-    traffic = counter_traffic(nodes)
+    counters = headline_counters(nodes)
+    traffic = issue = None
+    if counters:
+        per_step = int(counters["steps_per_launch"])
+        traffic = round(float(counters["hbm_bytes_per_launch"]) / per_step)
+        issue = float(counters["sq_insts_valu"]) / per_step / per_launch_s
     log("headline: %.1f MLUPS, kernel %.2f us, %.1f GB/s" % (mlups, per_launch_s * 1e6, achieved))
-    # The 151 MB single-buffer state of the 2048^2 headline stays in the 256 MB last-level
-    # cache, so its fraction of the HBM peak is not an HBM figure. The same kernel family at
-    # 4096^2 (604 MB per buffer, two buffers) runs from HBM; it is timed here too, next to a
-    # 1 GiB device copy (the practical HBM ceiling).
+    # At 2048^2 the states stay in the 256 MB last-level cache for the most part. At 4096^2 (604 MB
+    # per buffer, two buffers) the same kernel runs from HBM; it is timed here too, next to a 1 GiB
+    # device copy (the practical HBM ceiling).
     n4 = 4096
     log("HBM-resident reference: D2Q9 FP32 %dx%d tau %g" % (n4, n4, tau))
     r4, u4 = inputs.random_phase_turbulence_2d(n4, seed=0)
@@ -317,40 +335,47 @@ def main():
         plan = [
             ("d2q9_bgk_fp32_2048_two_buffers", lambda n: variant(
                 n, lambda: binding.Lattice(rho, u, tau=tau, streaming="two"), vs, 20, 72,
-                {"streaming": "two buffers (pull A -> B)"})),
+                {"streaming": "two buffers"}, steps_per_launch=STEPS_PER_LAUNCH["d2q9_bgk"])),
             ("d2q9_bgk_fp32_2048_forced", lambda n: variant(
                 n, lambda: binding.Lattice(rho, u, tau=tau, force=(1e-6, 0.0)), vs, 20, 72,
                 {"force": "uniform (1e-6, 0), shifted equilibrium",
-                 "streaming": "one buffer, in place"})),
+                 "streaming": "one buffer, through the read-out area and back"},
+                steps_per_launch=STEPS_PER_LAUNCH["d2q9_bgk"])),
             ("d2q9_bgk_fp32_4096", lambda n: variant(
                 n, lambda: binding.Lattice(*turb4(), tau=tau), vs, 20, 72,
-                {"streaming": "two buffers (automatic choice above 384 MiB)"})),
+                {"streaming": "two buffers (automatic choice above 384 MiB)"},
+                steps_per_launch=STEPS_PER_LAUNCH["d2q9_bgk"])),
             ("d3q27_bgk_fp32_256", lambda n: variant(
                 n, lambda: binding.Lattice(*tgv3(), lattice="D3Q27", tau=0.55, diag_every=100),
-                max(100, vs // 10), 10, 216, {"diag_every": 100})),
+                max(100, vs // 10), 10, 216, {"diag_every": 100},
+                steps_per_launch=STEPS_PER_LAUNCH["d3q27_bgk"])),
             ("d3q27_bgk_fp32_256_forced", lambda n: variant(
                 n, lambda: binding.Lattice(*tgv3(), lattice="D3Q27", tau=0.55,
                                            force=(1e-6, 0.0, 0.0)),
                 max(100, vs // 10), 10, 216, {"force": "uniform (1e-6, 0, 0)"})),
             ("d2q9_ddf_fp32_4096", lambda n: variant(
                 n, lambda: ddf_lattice("fp32"), max(100, vs // 4), 10, 144,
-                {"walls": "y", "phi": "central"})),
+                {"walls": "y", "phi": "central"},
+                steps_per_launch=STEPS_PER_LAUNCH["d2q9_ddf"])),
             ("d2q9_ddf_fp32_4096_sources", lambda n: variant(
                 n, lambda: ddf_lattice("fp32", force=(1e-7, 0.0), heat_source=1e-8),
                 max(100, vs // 4), 10, 144,
                 {"walls": "y", "phi": "central",
-                 "sources": "uniform force (1e-7, 0) and heat source 1e-8"})),
+                 "sources": "uniform force (1e-7, 0) and heat source 1e-8"},
+                steps_per_launch=STEPS_PER_LAUNCH["d2q9_ddf"])),
             ("d2q9_ddf_fp32_4096_prandtl", lambda n: variant(
                 n, lambda: ddf_lattice("fp32", prandtl=0.71, eta_over_mu=1.0),
                 max(100, vs // 4), 10, 144,
                 {"walls": "y", "phi": "central",
-                 "transport": "Pr 0.71 (heat flux q^c), eta/mu 1 (alpha theta div u)"})),
+                 "transport": "Pr 0.71 (heat flux q^c), eta/mu 1 (alpha theta div u)"},
+                steps_per_launch=STEPS_PER_LAUNCH["d2q9_ddf"])),
             ("d2q9_ddf_fp32_4096_neq_walls", lambda n: variant(
                 n, lambda: ddf_lattice("fp32", neq_walls=dict(u=((-0.05, 0.0), (0.05, 0.0)),
                                                               T=(0.8, 1.0))),
                 max(100, vs // 4), 10, 144,
                 {"walls": "y, non-equilibrium extrapolation (u_W = -+0.05, T_W = 0.8 / 1.0)",
-                 "wall_density": NEQ_DENSITY, "phi": "central"})),
+                 "wall_density": NEQ_DENSITY, "phi": "central"},
+                steps_per_launch=STEPS_PER_LAUNCH["d2q9_ddf"])),
             ("d2q9_ddf_fp32_4096_neq_walls_upwind", lambda n: variant(
                 n, lambda: ddf_lattice("fp32", phi=2,
                                        neq_walls=dict(u=((-0.05, 0.0), (0.05, 0.0)),
@@ -363,7 +388,8 @@ def main():
                 n, lambda: vdw_lattice(), max(100, vs // 4), 10, 144,
                 {"walls": "y", "phi": "central",
                  "eos": "van der Waals a = 0.27, b = 0.2 (T_cr 1.2, P_cr 0.25), rho 1, "
-                        "T 1.4 +- 0.03 shear layer"})),
+                        "T 1.4 +- 0.03 shear layer"},
+                steps_per_launch=STEPS_PER_LAUNCH["d2q9_ddf"])),
             ("d3q27_ddf_fp32_256", lambda n: variant(
                 n, lambda: binding.Lattice(*inputs.thermal_taylor_green_3d(256, 0.05),
                                            lattice="D3Q27", model="ddf", tau=0.6, phi=1),
@@ -425,7 +451,7 @@ def main():
                 binding, inputs, max(100, vs // 4), args.surrogate_inference_only)),
             ("d2q9_bgk_fp64_2048", lambda n: variant(
                 n, lambda: binding.Lattice(rho, u, tau=tau, storage="fp64"),
-                max(200, vs // 4), 20, 144)),
+                max(200, vs // 4), 20, 144, steps_per_launch=STEPS_PER_LAUNCH["d2q9_bgk"])),
         ]
         only = set(args.only.split(",")) if args.only else None
         if only and not only <= {name for name, _ in plan}:
@@ -458,19 +484,23 @@ def main():
                    "streaming": "one buffer, up to six steps per launch through the read-out area "
                                 "(151 MB state, automatic choice)",
                    "parity": "velocity rel-L2 <= 1e-5 vs FP64 oracle (tests/test_gpu_bgk.py)"},
-        # achieved = 72 bytes per node and step (9 float32 read + 9 written, what a step costs when
-        # every step goes through memory) x nodes / mean step time (HIP events on the context
-        # stream), priced against the 8 TB/s HBM peak: a launch takes several steps in LDS, so it
-        # may exceed the peak. hbm_resident is the same kernel at 4096^2, whose buffers do not fit
-        # the last-level cache; traffic is the counter bytes that leave the L2 towards the memory
-        # fabric per launch of six steps (last-level-cache hits included), from the committed profile of this
-        # kernel source.
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
+        # Launches of six steps are bound by vector issue: achieved = the vector instructions of a
+        # step (counters of the committed profile of this kernel source, null once the source has
+        # changed) / mean step time (HIP events on the context stream). hbm: the bytes of a state read
+        # and written once per six steps / mean step time, against the 8 TB/s HBM peak; hbm_resident is
+        # the same kernel at 4096^2, whose buffers do not fit the last-level cache. traffic: counter
+        # bytes that leave the L2 towards the memory fabric per step (last-level-cache hits included).
+        # one_step_equivalent: 72 bytes per node and step, which a run of one step per launch would
+        # have to move at this speed; not a share of any bandwidth.
+        "roofline": {"bound": "vector issue",
+                     "achieved": None if issue is None else round(issue / 1e9, 1),
+                     "peak": VALU_PEAK / 1e9, "unit": "G wavefront instructions/s",
+                     "frac": None if issue is None else round(issue / VALU_PEAK, 4),
+                     "hbm": {"achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                             "frac": round(achieved / HBM_PEAK_GBS, 4)},
+                     "one_step_equivalent": {"GBs": round(72 * nodes / per_launch_s / 1e9, 1)},
                      "traffic": traffic,
-                     "level": "LDS: six steps per launch between a read and a write of the state, so "
-                              "this fraction is not a share of the memory bandwidth",
-                     "traffic_kind": "L2-to-fabric bytes (FETCH_SIZE + WRITE_SIZE), "
+                     "traffic_kind": "L2-to-fabric bytes per step (FETCH_SIZE + WRITE_SIZE), "
                                      "last-level-cache hits included",
                      "hbm_resident": {"workload": "D2Q9 BGK 4096x4096 FP32, two buffers "
                                                   "(604 MB each), same recipe",

@@ -58,10 +58,13 @@ extern "C" {
 #define LBM_COLLIDE_MLP 1   /* learned surrogate with per-node fallback to the paper's collision */
 
 /* Streaming layout of the population state (isothermal model, D2Q9 or D3Q27, with FP32/FP64
-   storage and the paper's collision; every other configuration uses two buffers). */
+   storage and the paper's collision; every other configuration uses two buffers). Several steps per
+   launch (D2Q9) go from one buffer into the other: from A to B and on, or from the one buffer into
+   the read-out area and back. */
 #define LBM_STREAM_AUTO 0        /* one buffer when its size is at most 384 MiB, else two */
 #define LBM_STREAM_TWO_BUFFERS 1 /* pull from buffer A, write buffer B, swap */
-#define LBM_STREAM_ONE_BUFFER 2  /* in place, alternating two access patterns (half the memory) */
+#define LBM_STREAM_ONE_BUFFER 2  /* in place, alternating two access patterns, one step per launch
+                                    (least memory: a read-out area of 8 (D + 3) bytes per node) */
 
 typedef struct lbm_ctx lbm_ctx; /* opaque; owned by the library */
 
@@ -137,7 +140,7 @@ void lbm_default_params(lbm_params* p);
    one-buffer layout takes several steps per launch through the read-out area, that area is as
    large as a state: 72 bytes per node instead of 40 for LBM_STORE_FP64, the padded rows for
    small or ragged LBM_STORE_FP32 lattices. lbm_create also takes a workspace without this part
-   (and without the records of the lower windows of some D2Q9 DDF lattices, up to 26 KB) and then
+   (and without the records of the lower windows of some D2Q9 DDF lattices, some KB) and then
    runs one step per launch, with the same results. */
 int lbm_workspace_size(const lbm_params* p, size_t* bytes);
 

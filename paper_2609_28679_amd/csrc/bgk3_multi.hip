@@ -8,11 +8,12 @@
 // right of the tile is a wavefront of its own (a node per lane), so rows stay 64 aligned columns
 // wide; the rows above and below cost 11 wavefronts of arithmetic for 9 rows. The next plane's loads
 // are issued before the second step. Twelve wavefronts, three per SIMD, 168 registers, 78 KB of
-// LDS. Measured on MI355X, us per step, one -> two steps per launch: 256^3 619 -> 460, 180 x 170 x
-// 160 236 -> 153. Region rows at 256^3: 11 460 us, 7 524, 14 882 (128 registers, spilled). With
-// walls or a force the second collision spills at 168 registers: 612 -> 666 us and 619 -> 800 (597
-// and 580 at 7 rows), so those runs keep one step per launch; lattices of one in-place buffer do
-// too (100^3: 41 us either way).
+// LDS. Measured on MI355X, us per step, one -> two steps per launch: 256^3 619 -> 457, 160 x 180 x
+// 170 197 -> 151. Region rows at 256^3: 11 460 us, 7 524, 14 882 (128 registers, spilled). Where it
+// is taken: routes.h. What keeps one step per launch: walls and forces, whose second collision
+// spills at 168 registers (256^3 612 -> 666 us and 619 -> 800; at 7 rows, without spills, 597 and 580,
+// which a kernel of its own would give), and lattices of one in-place buffer (us per step in place /
+// two buffers and two steps: 100^3 41 / 41, 120^3 58 / 58, but 140^3 140 / 99 and 150^3 154 / 111).
 #include "bgk_common.h"
 #include "routes.h"
 

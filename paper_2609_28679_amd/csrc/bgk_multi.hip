@@ -4,9 +4,12 @@
 // One step per launch moves 72 bytes per node and step (float32) and is bound by that traffic;
 // its arithmetic, 90 vector instructions per node, fills a fifth of the time. Six steps per
 // launch move the state once for all six and recompute the nodes around each tile (1.4 x the
-// arithmetic), which leaves the two about level. Measured on MI355X, us per step, one-step
-// kernels -> this one: float32 64^2 2.54 -> 0.99 (launches), 2048^2 44.2 -> 24.3, 4096^2 210 ->
-// 86.7; float64 1001 x 515 11.3 -> 5.1, 2048^2 97.2 -> 39.4.
+// arithmetic), which leaves the two about level. Measured on MI355X, us per step in calls of 600
+// steps and more, one-step kernels -> this one: float32 64^2 2.54 -> 0.97 (launches), 2048^2 44.2 ->
+// 22.1, with a force 45.9 -> 33.4, 4096^2 210 -> 88; float64 1001 x 515 11.3 -> 4.6, with walls and
+// force 5.3, 2048^2 98 -> 37.8. Calls of 20 steps: 2048^2 24-27, 4096^2 99-109, float64 2048^2 43;
+// one that begins at an odd step of the in-place layout also takes one or two one-step launches
+// (2048^2 29.8).
 #include "bgk_common.h"
 #include "routes.h"
 

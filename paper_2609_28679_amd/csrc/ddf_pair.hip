@@ -6,9 +6,10 @@
 // Here a workgroup of 256 columns walks a tall window bottom to top and takes every row through
 // both steps: the first step's rows go through LDS to the second one, 75 bytes per node and step
 // from memory and no row of the window read twice (three halo rows each way, of about 137 at
-// 4096^2). Measured on MI355X, us per step, one step -> two per launch: 4096^2 walls 562 -> 355,
-// 2048^2 plain 143 -> 103, force and heat source 167 -> 116, Pr 0.71 with NEQ walls 177 -> 125, van
-// der Waals 194 -> 134, 1021 x 509 Pr 0.71 with NEQ walls 30.6 -> 28.3.
+// 4096^2). Measured on MI355X, us per step, one step -> two per launch: 4096^2 with walls 562 -> 324
+// to 355, with force and heat source 582 -> 435, Pr 0.71 601 -> 450, NEQ walls 561 -> 365; 2048^2 plain
+// 143 -> 89 to 103, force and heat source 167 -> 117, Pr 0.71 with NEQ walls 177 -> 127, van der Waals
+// 194 -> 137; 1021 x 509 Pr 0.71 with NEQ walls 30.6 -> 27.7. Where it is taken: routes.h.
 //
 // One iteration, row r, one barrier:
 //   gather   first step: row r (loaded during the iteration before), its moments; second step:

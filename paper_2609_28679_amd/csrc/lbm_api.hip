@@ -274,9 +274,10 @@ void make_plan(const lbm_params* p, Plan& P, bool compact = false) {
   if (P.ddf && P.D == 3)  // the one-launch step and the upwind sweeps have their own grids
     P.partial_slots = (int)std::max<int64_t>(P.partial_slots, ddf3_max_records(P.L, P.G));
   // One in-place buffer where supported and either requested or small enough to profit from
-  // the 256 MB last-level cache. Measured float32 D2Q9 step times (one vs two buffers): 44 vs
-  // 51 us at 151 MB per buffer, 122 vs 131 us at 340 MB, equal at 399 MB, 235 vs 209 us at
-  // 604 MB; the crossover is taken as 384 MiB.
+  // the 256 MB last-level cache. Measured float32 D2Q9 step times with one step per launch (one
+  // vs two buffers): 44 vs 51 us at 151 MB per buffer, 122 vs 131 us at 340 MB, equal at 399 MB,
+  // 235 vs 209 us at 604 MB; the crossover is taken as 384 MiB. With several steps per launch the
+  // one buffer of D2Q9 goes through the read-out area and back, 22 vs 22-27 us at 151 MB.
   const bool aa_ok = !P.ddf && P.codec < 0 && p->collision == LBM_COLLIDE_PLAIN;
   const size_t one_buffer = (size_t)P.planes * P.L.plane * P.elem;
   P.aa = aa_ok && (p->streaming == LBM_STREAM_ONE_BUFFER ||

@@ -1,7 +1,7 @@
 // Learned collision surrogate: 12 -> 64 -> 64 -> 9 network on bfloat16 matrix cores.
 //
-// All three layers are evaluated in transposed form, Z^T = W H^T, one wavefront per 64 samples,
-// with v_mfma_f32_16x16x16_bf16 (D = A B + C, A 16x16 rows = output features, B 16x16 columns
+// All three layers are evaluated in transposed form, Z^T = W H^T, in tiles of 16 samples (training:
+// one per wavefront; inference: one or four, see k_mlp_forward), with v_mfma_f32_16x16x16_bf16 (D = A B + C, A 16x16 rows = output features, B 16x16 columns
 // = samples, float32 accumulation). Register layout of the 64 lanes l (j = 0..3):
 //   A (M x K):  A[l % 16][4 (l / 16) + j]
 //   B (K x N):  B[4 (l / 16) + j][l % 16]
@@ -30,9 +30,6 @@ constexpr float kSNeq = 1024.0f, kSU = 16.0f;
 
 // float32 -> bfloat16, round to nearest even (lowered to v_cvt_pk_bf16_f32 on gfx950)
 __device__ __forceinline__ short f2bf(float f) { return __builtin_bit_cast(short, (__bf16)f); }
-__device__ __forceinline__ float bf2f(short h) {
-  return __uint_as_float(((uint32_t)(uint16_t)h) << 16);
-}
 
 __device__ __forceinline__ f32x4 mfma16(bf16x4 a, bf16x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
@@ -161,13 +158,12 @@ __device__ __forceinline__ f32x4 mlp_forward_tile32(const MlpLdsP& s, const shor
                                                     int n) {
   const int lane = threadIdx.x & 63;
   const int r = lane & 15, q = lane >> 4;
-  const int rz = r;
   const bf16x4 xb = ld4(&xs[16 * n + r][4 * q]);
   bf16x4 h1[4], h2[4];
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
     f32x4 acc = bias4(s.b1 + 16 * m, lane);
-    acc = mfma16(ld4(&s.w1[16 * m + rz][4 * q]), xb, acc);
+    acc = mfma16(ld4(&s.w1[16 * m + r][4 * q]), xb, acc);
 #pragma unroll
     for (int j = 0; j < 4; ++j) h1[m][j] = f2bf(gelu(acc[j]));
   }
@@ -176,8 +172,8 @@ __device__ __forceinline__ f32x4 mlp_forward_tile32(const MlpLdsP& s, const shor
     f32x4 acc = bias4(s.b2 + 16 * m, lane);
 #pragma unroll
     for (int p = 0; p < 2; ++p)
-      acc = mfma32(cat8(ld4(&s.w2[16 * m + rz][32 * p + 4 * q]),
-                        ld4(&s.w2[16 * m + rz][32 * p + 16 + 4 * q])),
+      acc = mfma32(cat8(ld4(&s.w2[16 * m + r][32 * p + 4 * q]),
+                        ld4(&s.w2[16 * m + r][32 * p + 16 + 4 * q])),
                    cat8(h1[2 * p], h1[2 * p + 1]), acc);
 #pragma unroll
     for (int j = 0; j < 4; ++j) h2[m][j] = f2bf(gelu(acc[j]));
@@ -185,7 +181,7 @@ __device__ __forceinline__ f32x4 mlp_forward_tile32(const MlpLdsP& s, const shor
   f32x4 acc = bias4(s.b3, lane);
 #pragma unroll
   for (int p = 0; p < 2; ++p)
-    acc = mfma32(cat8(ld4(&s.w3[rz][32 * p + 4 * q]), ld4(&s.w3[rz][32 * p + 16 + 4 * q])),
+    acc = mfma32(cat8(ld4(&s.w3[r][32 * p + 4 * q]), ld4(&s.w3[r][32 * p + 16 + 4 * q])),
                  cat8(h2[2 * p], h2[2 * p + 1]), acc);
   return acc;
 }
