@@ -613,7 +613,8 @@ hipError_t launch_ddf(int fmt, bool walls, bool pull, const void* A, void* B, co
                       const Grid& G0, const DdfParams& prm, float s_enc, float s_dec,
                       double* partials, void* nb, int* records, hipStream_t s) {
   if (prm.ext() && fmt >= 2) return hipErrorInvalidValue;  // no extended path with reduced storage
-  const Grid G = ddf_step_grid(G0, L, prm.phi, fmt, prm.ext() || prm.eos,
+  const DdfCollision c = prm.eos ? kDdfVdw : (prm.ext() ? kDdfExtended : kDdfPlain);
+  const Grid G = ddf_step_grid(G0, L, prm.phi, fmt, c, walls && !prm.neq,
                                partials && records ? *records : INT_MAX);
   if (records) *records = G.blocks();
   if (prm.neq) {

@@ -42,11 +42,22 @@ inline Grid make_grid_ddf(const Layout& L, int halo, bool reduced) {
 // steps keep their 4 (552 / 568 at 6 and 561 / 580).
 constexpr int kDdfExtRows = 8;
 
+// The collision of a step: plain, with sources or transport control, of a van der Waals fluid.
+enum DdfCollision { kDdfPlain, kDdfExtended, kDdfVdw };
+
+// Workgroups that share a compute unit, by the registers of the kernel (wavefronts per SIMD in the
+// compiler's resource report): three of the plain float32 step with central Phi, one of the upwind
+// steps in float64 or of a van der Waals fluid or between bounce-back walls, all but the plain ones;
+// two otherwise.
+inline int ddf_per_cu(int halo, int fmt, DdfCollision c, bool bounce) {
+  if (fmt == 0 && halo == 1 && c == kDdfPlain) return 3;
+  return halo == 2 && c != kDdfPlain && (fmt == 1 || c == kDdfVdw || bounce) ? 1 : 2;
+}
+
 // Window rows that the chip walks one after the other: rounds of resident workgroups x (rows + 2
-// halo + 1 for the start), in tenths. Two workgroups share a compute unit, three of the plain
-// float32 step with central Phi; each of the three beyond the first costs a fifth where all
-// workgroups are resident at once (700 x 640: 4 rows, two workgroups per unit, 19.3 us; 3 rows,
-// three per unit, 21.5).
+// halo + 1 for the start), in tenths. Each of three workgroups of a unit beyond the first costs a
+// fifth where all workgroups are resident at once (700 x 640: 4 rows, two workgroups per unit, 19.3
+// us; 3 rows, three per unit, 21.5).
 inline int64_t ddf_turns(int64_t blocks, int rows, int halo, int per_cu) {
   int64_t rounds = 10 * div_up(blocks, (int64_t)kCus * per_cu);
   if (per_cu == 3 && rounds == 10) rounds += 2 * (div_up(blocks, kCus) - 1);
@@ -59,8 +70,8 @@ inline int64_t ddf_turns(int64_t blocks, int rows, int halo, int per_cu) {
 // upwind 28.1 -> 7.9, float16 44.6 -> 11.5, Pr 0.71 with NEQ walls 21.9 -> 10.5; 512^2 plain 16.0 ->
 // 13.8, upwind 38.5 -> 22; 1021 x 509 Pr 0.71 with NEQ walls 38.3 -> 30.6, float16 48.7 -> 32. Of 28
 // sizes from 40 x 20 to 2048^2 in 18 configurations these rows are within 3% of the best ones on
-// average (512^2 with a force 4 rows 17.9, 2 rows 18.2). They are not the best for each: upwind Phi
-// with a van der Waals fluid runs 270 x 2000 5% faster on the fixed 16 rows.
+// average (512^2 with a force 4 rows 17.9, 2 rows 18.2; 768^2 float64 Pr 0.71 upwind 12 rows 54.4, 16
+// rows 65.1).
 inline Grid ddf_fill(Grid G, const Layout& L, int halo, int per_cu) {
   auto turns = [&](int r) { return ddf_turns(G.nbx * div_up(L.ny, r), r, halo, per_cu); };
   int64_t best = -1;
@@ -79,8 +90,9 @@ inline Grid ddf_fill(Grid G, const Layout& L, int halo, int per_cu) {
 // Launch grid of one step, from the plan's grid: taller windows for the extended collisions. A step
 // that writes its diagnostics records keeps the plan's windows where the lower ones would write
 // more than there is room for.
-inline Grid ddf_step_grid(Grid G, const Layout& L, int phi, int fmt, bool extended, int room) {
-  if (fmt < 2 && extended && G.rows < kDdfExtRows) {
+inline Grid ddf_step_grid(Grid G, const Layout& L, int phi, int fmt, DdfCollision c, bool bounce,
+                          int room) {
+  if (fmt < 2 && c != kDdfPlain && G.rows < kDdfExtRows) {
     G.rows = kDdfExtRows;
     fit_rows(G, L.ny);
   }
@@ -88,14 +100,17 @@ inline Grid ddf_step_grid(Grid G, const Layout& L, int phi, int fmt, bool extend
   // rounds: 13 rows 146 us, 16 rows 137; 3000^2 15 rows 305, 16 rows 282-295)
   if (fmt >= 2 && G.blocks() > 2 * 2 * kCus) return G;
   const int halo = phi == 2 ? 2 : 1;
-  const Grid filled = ddf_fill(G, L, halo, fmt == 0 && halo == 1 && !extended ? 3 : 2);
+  const Grid filled = ddf_fill(G, L, halo, ddf_per_cu(halo, fmt, c, bounce));
   return filled.blocks() <= room ? filled : G;
 }
 
 // Most diagnostics records any step of the format writes (grid G of the plan).
 inline int ddf_max_records(const Layout& L, const Grid& G, int phi, int fmt) {
-  return std::max(ddf_step_grid(G, L, phi, fmt, false, INT_MAX).blocks(),
-                  ddf_step_grid(G, L, phi, fmt, true, INT_MAX).blocks());
+  int most = 0;
+  for (DdfCollision c : {kDdfPlain, kDdfExtended, kDdfVdw})
+    for (bool bounce : {false, true})
+      most = std::max(most, ddf_step_grid(G, L, phi, fmt, c, bounce, INT_MAX).blocks());
+  return most;
 }
 
 // ---- double distribution, D2Q9: two steps per launch ----------------------------------------------
@@ -149,7 +164,7 @@ inline bool ddf_pair_supported(int fmt, const Layout& L, const DdfParams& prm, c
   if (!ext) return true;
   const bool sparse = (int64_t)L.nx * 100 < (int64_t)s.nbx * s.threads * 63;
   if (prm.neq && s.rounds > 1 && s.rows < 16) return false;
-  const Grid one = ddf_step_grid(make_grid_ddf(L, 1, false), L, prm.phi, 0, true, INT_MAX);
+  const Grid one = ddf_step_grid(make_grid_ddf(L, 1, false), L, prm.phi, 0, kDdfExtended, false, INT_MAX);
   // one-step turns in tenths
   return s.turns * 1000 <= ddf_turns(one.blocks(), one.rows, 1, 2) * (sparse ? 190 : (prm.neq ? 300 : 246));
 }

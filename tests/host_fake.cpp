@@ -109,9 +109,9 @@ int fake_ddf_records(int nx, int ny, int phi, int fmt) {
   const lbm::Layout L = lbm::make_layout(nx, ny, 1, 4);
   return lbm::ddf_max_records(L, lbm::make_grid_ddf(L, phi == 2 ? 2 : 1, fmt >= 2), phi, fmt);
 }
-int fake_ddf_rows(int nx, int ny, int phi, int fmt, int ext) {
+int fake_ddf_rows(int nx, int ny, int phi, int fmt, int collision, int bounce) {
   const lbm::Layout L = lbm::make_layout(nx, ny, 1, 4);
-  return lbm::ddf_step_grid(lbm::make_grid_ddf(L, phi == 2 ? 2 : 1, fmt >= 2), L, phi, fmt, ext, 1 << 30).rows;
+  return lbm::ddf_step_grid(lbm::make_grid_ddf(L, phi == 2 ? 2 : 1, fmt >= 2), L, phi, fmt, (lbm::DdfCollision)collision, bounce, 1 << 30).rows;
 }
 int fake_bgk3_pair(int nx, int ny, int nz) {
   const lbm::Layout L = lbm::make_layout(nx, ny, nz, 4);

@@ -308,8 +308,9 @@ def test_two_ddf_steps_per_launch_where_they_are_faster(fake, options):
         assert fake.fake_ddf_pair(nx, ny, *options) == 0, (nx, ny)
 
 
-@pytest.mark.parametrize("nx,ny,phi,fmt,ext,rows", [
-    (700, 640, 1, 0, 0, 4),   # 19.3 us a step; 3 rows 21.8
+# collisions: 0 plain, 1 sources or transport control, 2 van der Waals; us a step
+@pytest.mark.parametrize("nx,ny,phi,fmt,collision,rows", [
+    (700, 640, 1, 0, 0, 4),   # 19.3; 3 rows 21.8
     (512, 512, 1, 0, 0, 2),   # 14.0; 4 rows 16.0
     (640, 500, 1, 0, 0, 2),   # 15.4; 4 rows 18.0
     (2048, 2048, 1, 0, 0, 4),
@@ -320,9 +321,14 @@ def test_two_ddf_steps_per_launch_where_they_are_faster(fake, options):
     (512, 512, 1, 0, 1, 4),   # 17.9; 8 rows 22.7
     (1021, 509, 1, 0, 1, 5),  # 24.8; 8 rows 32.1
     (64, 64, 2, 0, 0, 1),
+    (270, 2000, 2, 0, 2, 16),  # 52.3; 8 rows 55.9
+    (270, 2000, 2, 1, 1, 16),  # 56.9; 8 rows 62.5
+    (768, 768, 2, 1, 1, 12),   # 54.4; 6 rows 68.7
+    (768, 768, 2, 0, 2, 12),   # 43.7; 6 rows 50.2
+    (1024, 1024, 2, 0, 1, 11),
 ])
-def test_window_rows_of_one_ddf_step(fake, nx, ny, phi, fmt, ext, rows):
-    assert fake.fake_ddf_rows(nx, ny, phi, fmt, ext) == rows
+def test_window_rows_of_one_ddf_step(fake, nx, ny, phi, fmt, collision, rows):
+    assert fake.fake_ddf_rows(nx, ny, phi, fmt, collision, 0) == rows
 
 
 def test_two_d3q27_steps_per_launch_where_they_are_faster(fake):
